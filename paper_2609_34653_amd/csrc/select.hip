@@ -1,16 +1,15 @@
 // Budgeted whole-unit selection, one workgroup per segment.  Up to 512 units: a single wave
-// (select_small_kernel); beyond: 1024 threads with all state in LDS (select_kernel).
+// (select_small_kernel); beyond: 1024 threads (select_kernel).
 //
 // Groups (paper: must-keep, recent-context, selected-history):
 //   protected  units holding a system token (all kept; over budget -> OMNITIDE_E_BUDGET)
 //   recent     newest live non-system units whose suffix total fits min(R, B - T_sys); because
 //              lengths are positive the suffix total grows monotonically, so "walk newest to
 //              oldest and stop at the first misfit" is the set {u : suffix(u) <= cap}
-//   selected   remaining live units sorted by the 64-bit key (score << 13 | id) descending
-//              (bitonic sort in LDS), kept while the inclusive prefix of their lengths fits;
-//              the prefix sum grows monotonically, so "stop at the first misfit" is again a
-//              threshold on the prefix.
-// Thread t owns the consecutive units [t*per, (t+1)*per), per = ceil(U / 1024) <= 8.
+//   selected   remaining live units in descending order of the 64-bit key (score << 13 | id),
+//              kept while the inclusive prefix of their lengths fits; the prefix sum grows
+//              monotonically, so "stop at the first misfit" is a threshold on the key, found by
+//              a radix select without sorting.
 #include "common.h"
 #include "kernels.h"
 
@@ -38,40 +37,73 @@ __device__ inline uint64_t udiv64(uint64_t n, uint32_t d) {
   return n / d;
 }
 
+// Beyond 512 units: the budget cut by the same radix select as the single-wave variant below,
+// over a workgroup.  Thread t owns units [t*per, (t+1)*per); its keys stay in registers.  Digits
+// are 12 bits (4,096 buckets; thread t scans buckets 4095 - 4t .. 4092 - 4t, highest first) and
+// start at the highest bit in which two candidates differ, so the first pass already spreads
+// the candidates over most buckets and two or three passes end the search.  A bucket holds its
+// candidates' token total (low 44 bits) and their number (high 20) in one 64-bit LDS atomic.
+// Bound by latency: barriers and LDS round trips of one workgroup.  A full bitonic sort of the
+// keys in LDS (78 barrier-separated steps at 4,096) took 74.5 us at 3,880 units; this takes
+// about 15 us (score and selection together 117.5 -> 57.7 us).
+constexpr int kWideDigitBits = 12;
+constexpr int kWideBuckets = 1 << kWideDigitBits;
+constexpr int kWidePer = kWideBuckets / kSelThreads;
+constexpr int kSelWaves = kSelThreads / kWave;
+constexpr int kCountShift = 44;
+static_assert(kSelWaves == 16, "wave totals are read by lanes 0..15");
+static_assert(kMaxUnits < (1 << (64 - kCountShift)), "a bucket's count field");
+
+__device__ inline uint64_t wave_or_u64(uint64_t v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off, kWave);
+  return v;
+}
+
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const uint64_t* __restrict__ wsum_g, const int32_t* __restrict__ len_g,
     const int32_t* __restrict__ first_g, const int32_t* __restrict__ last_g,
     const uint32_t* __restrict__ flags_g, int n_units, int budget, int recent,
     uint64_t* __restrict__ score_g, uint8_t* __restrict__ keep_g,
     int32_t* __restrict__ kept_tokens_g, int32_t* __restrict__ status) {
-  __shared__ uint64_t keys[kMaxUnits];
-  __shared__ int32_t lens[kMaxUnits];
-  __shared__ uint8_t chosen[kMaxUnits];
-  __shared__ int32_t scr_i[kSelThreads / kWave + 1];
+  __shared__ __attribute__((aligned(16))) unsigned long long hist[kWideBuckets];
+  __shared__ int32_t w_max[kSelWaves], w_elig[kSelWaves], w_sys[kSelWaves], w_err[kSelWaves];
+  __shared__ int32_t w_rec[kSelWaves], w_bad[kSelWaves], w_tot[kSelWaves];
+  __shared__ uint64_t w_or[kSelWaves], w_zero[kSelWaves];
+  __shared__ int32_t s_cut, s_taken, s_left, s_all;
 
   const int seg = blockIdx.x;
   const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int U = n_units;
   const int per = (U + kSelThreads - 1) / kSelThreads;
   const int u0 = tid * per;
   const size_t base = static_cast<size_t>(seg) * U;
 
   int ln[kPer], fs[kPer], ls[kPer];
-  bool sys[kPer];
-  uint64_t sc[kPer];
-  bool bad = false, big = false;
-  int my_max_first = -1;
   uint32_t fl[kPer];
   uint64_t ws[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {           // all loads first: one memory round trip
-    const int u = min(u0 + i, U - 1);
-    ln[i] = len_g[base + u];
-    fs[i] = first_g[base + u];
-    ls[i] = last_g[base + u];
-    fl[i] = flags_g[base + u];
-    ws[i] = wsum_g[base + u];
+    ln[i] = fs[i] = ls[i] = 0;
+    fl[i] = 0;
+    ws[i] = 0;
+    if (i < per) {                           // uniform
+      const int u = min(u0 + i, U - 1);
+      ln[i] = len_g[base + u];
+      fs[i] = first_g[base + u];
+      ls[i] = last_g[base + u];
+      fl[i] = flags_g[base + u];
+      ws[i] = wsum_g[base + u];
+    }
   }
+#pragma unroll
+  for (int j = 0; j < kWidePer; ++j) hist[kWidePer * tid + j] = 0;
+  bool sys[kPer];
+  uint64_t key[kPer];
+  bool bad = false, big = false;
+  int my_max_first = -1, my_sys = 0, my_elig = 0;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     const int u = u0 + i;
@@ -79,19 +111,43 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     if (!mine || ln[i] <= 0) ln[i] = 0;
     const bool live = ln[i] > 0;
     sys[i] = live && (fl[i] & 1u) != 0;
-    sc[i] = live ? udiv64(ws[i], static_cast<uint32_t>(ln[i])) : 0;
+    const uint64_t sc = live ? udiv64(ws[i], static_cast<uint32_t>(ln[i])) : 0;
     bad |= live && (ls[i] - fs[i] + 1) != ln[i];
-    big |= (sc[i] >> kScoreBits) != 0;          // the ranking key holds kScoreBits of score
+    big |= (sc >> kScoreBits) != 0;          // the ranking key holds kScoreBits of score
     if (live) my_max_first = max(my_max_first, fs[i]);
-    if (mine) {
-      score_g[base + u] = sc[i];
-      chosen[u] = 0;
-      lens[u] = ln[i];
-    }
+    my_sys += sys[i] ? ln[i] : 0;
+    my_elig += (live && !sys[i]) ? ln[i] : 0;
+    if (mine) score_g[base + u] = sc;
+    key[i] = (sc << kIdBits) | static_cast<uint64_t>(mine ? u : 0);
   }
+  // wave totals, then every wave combines the 16 waves' (lane l < 16 holds wave l's)
+  const int inc_max = wave_scan_max_i32(my_max_first, -1);
+  const int inc_elig = wave_scan_add_i32(my_elig);
+  const int sum_sys = static_cast<int>(wave_sum_u32(static_cast<uint32_t>(my_sys)));
+  const int err = (__any(bad) ? 1 : 0) | (__any(big) ? 2 : 0);
+  if (lane == kWave - 1) {
+    w_max[wave] = inc_max;
+    w_elig[wave] = inc_elig;
+    w_sys[wave] = sum_sys;
+    w_err[wave] = err;
+  }
+  __syncthreads();
+  const bool has = lane < kSelWaves;
+  const int all_max = has && lane < wave ? w_max[lane & 15] : -1;
+  const int all_elig = has ? w_elig[lane & 15] : 0;
+  const int all_err = has ? w_err[lane & 15] : 0;
+  const int max_before = wave_max_i32(all_max);
+  const int elig_before_wave =
+      static_cast<int>(wave_sum_u32(static_cast<uint32_t>(lane < wave ? all_elig : 0)));
+  const int elig_total = static_cast<int>(wave_sum_u32(static_cast<uint32_t>(all_elig)));
+  const int t_sys =
+      static_cast<int>(wave_sum_u32(static_cast<uint32_t>(has ? w_sys[lane & 15] : 0)));
+  bool any_bad = __any((all_err & 1) != 0);
+  const bool any_big = __any((all_err & 2) != 0);
+
   // live units must appear in unit order: each first slot exceeds every earlier live unit's
-  int ignored;
-  int run = block_exclusive_max(my_max_first, -1, scr_i, &ignored);
+  int run = max(max_before, dpp_move<kDppWaveShr1, 0xf>(-1, inc_max));
+  bad = false;
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     if (ln[i] > 0) {
@@ -99,33 +155,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       run = max(run, fs[i]);
     }
   }
-  const int n_bad = block_sum(bad ? 1 : 0, scr_i);
-  const int n_big = block_sum(big ? 1 : 0, scr_i);
-
-  int my_sys = 0;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) my_sys += sys[i] ? ln[i] : 0;
-  const int t_sys = block_sum(my_sys, scr_i);
-
-  if (n_bad > 0 || n_big > 0 || t_sys > budget) {
-    for (int u = tid; u < U; u += kSelThreads) keep_g[base + u] = 0;
-    if (tid == 0) {
-      kept_tokens_g[seg] = 0;
-      set_status(status, n_bad > 0   ? OMNITIDE_E_TAGS
-                         : n_big > 0 ? OMNITIDE_E_RANGE
-                                     : OMNITIDE_E_BUDGET);
-    }
-    return;
-  }
-
   // recent window: suffix sums of eligible (live, non-system) lengths
   const int cap_rec = min(recent, budget - t_sys);
-  int my_elig = 0;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) my_elig += (ln[i] > 0 && !sys[i]) ? ln[i] : 0;
-  int elig_total;
-  const int elig_before = block_exclusive_scan(my_elig, scr_i, &elig_total);
-  int suffix = elig_total - elig_before - my_elig;   // eligible tokens in later threads
+  int suffix = elig_total - elig_before_wave - inc_elig;   // eligible tokens in later threads
   bool rec[kPer];
   int my_rec = 0;
 #pragma unroll
@@ -137,70 +169,118 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       my_rec += rec[i] ? ln[i] : 0;
     }
   }
-  const int t_rec = block_sum(my_rec, scr_i);
+  // candidates (state: 1 active, 2 kept, 0 dropped), and the bits in which their keys differ
+  int state[kPer];
+  uint64_t k_or = 0, k_zero = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    state[i] = (ln[i] > 0 && !sys[i] && !rec[i]) ? 1 : 0;
+    k_or |= state[i] ? key[i] : 0;
+    k_zero |= state[i] ? ~key[i] : 0;
+  }
+  k_or = wave_or_u64(k_or);
+  k_zero = wave_or_u64(k_zero);
+  const int sum_rec = static_cast<int>(wave_sum_u32(static_cast<uint32_t>(my_rec)));
+  const bool wave_bad = __any(bad);
+  if (lane == 0) {
+    w_or[wave] = k_or;
+    w_zero[wave] = k_zero;
+    w_rec[wave] = sum_rec;
+    w_bad[wave] = wave_bad ? 1 : 0;
+  }
+  __syncthreads();
+  any_bad |= __any(has && w_bad[lane & 15] != 0);
+  if (any_bad || any_big || t_sys > budget) {
+    for (int u = tid; u < U; u += kSelThreads) keep_g[base + u] = 0;
+    if (tid == 0) {
+      kept_tokens_g[seg] = 0;
+      set_status(status, any_bad   ? OMNITIDE_E_TAGS
+                         : any_big ? OMNITIDE_E_RANGE
+                                   : OMNITIDE_E_BUDGET);
+    }
+    return;
+  }
+  const int t_rec =
+      static_cast<int>(wave_sum_u32(static_cast<uint32_t>(has ? w_rec[lane & 15] : 0)));
+  const uint64_t differ = wave_or_u64(has ? w_or[lane & 15] : 0) &
+                          wave_or_u64(has ? w_zero[lane & 15] : 0);
   const int cap_sel = budget - t_sys - t_rec;
 
-  // candidates sorted by (score desc, id desc); key 0 = not a candidate (sorts last)
-  int P = 1;
-  while (P < U) P <<= 1;
+  // Radix select of the first misfit in (score desc, id desc) order.  All active keys agree above
+  // bit hi.  With one candidate (or none) no bits differ and one digit of width 1 decides.
+  int taken = 0;                                    // tokens kept by the search so far
+  int hi = max(64 - __builtin_clzll(differ | 1), 1);
+  while (true) {
+    const int lo = max(hi - kWideDigitBits, 0);
+    const uint64_t mask = (1ull << (hi - lo)) - 1;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int u = u0 + i;
-    if (i < per && u < U) {
-      const bool cand = ln[i] > 0 && !sys[i] && !rec[i];
-      keys[u] = cand ? ((sc[i] << kIdBits) | static_cast<uint64_t>(u)) + 1 : 0;
+    for (int i = 0; i < kPer; ++i)
+      if (state[i] == 1)
+        atomicAdd(&hist[(key[i] >> lo) & mask],
+                  (1ull << kCountShift) + static_cast<uint32_t>(ln[i]));
+    __syncthreads();
+    // buckets top + kWidePer - 1 .. top, read highest first and cleared for the next pass
+    const int top = kWideBuckets - kWidePer * (tid + 1);
+    uint64_t hv[kWidePer];
+    int hsum = 0;
+#pragma unroll
+    for (int j = 0; j < kWidePer; ++j) {
+      hv[j] = hist[top + kWidePer - 1 - j];
+      hsum += static_cast<int>(hv[j] & ((1ull << kCountShift) - 1));
     }
-  }
-  for (int u = U + tid; u < P; u += kSelThreads) keys[u] = 0;
-  __syncthreads();
-  for (int kk = 2; kk <= P; kk <<= 1) {
-    for (int j = kk >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < P; i += kSelThreads) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const uint64_t a = keys[i], b = keys[ixj];
-          const bool desc = (i & kk) == 0;
-          if (desc ? (a < b) : (a > b)) {
-            keys[i] = b;
-            keys[ixj] = a;
-          }
+#pragma unroll
+    for (int j = 0; j < kWidePer; ++j) hist[top + j] = 0;
+    const int inc = wave_scan_add_i32(hsum);
+    if (lane == kWave - 1) w_tot[wave] = inc;
+    if (tid == 0) s_cut = -1;
+    __syncthreads();
+    const int before_wave = static_cast<int>(
+        wave_sum_u32(static_cast<uint32_t>(has && lane < wave ? w_tot[lane & 15] : 0)));
+    int acc = taken + before_wave + inc - hsum;
+    if (acc <= cap_sel && acc + hsum > cap_sel) {   // the first misfit is in this thread's range
+      bool open = true;
+#pragma unroll
+      for (int j = 0; j < kWidePer; ++j) {
+        const int h = static_cast<int>(hv[j] & ((1ull << kCountShift) - 1));
+        if (open && acc + h > cap_sel) {
+          s_cut = top + kWidePer - 1 - j;
+          s_taken = acc;
+          s_left = static_cast<int>(hv[j] >> kCountShift);
+          open = false;
         }
+        acc += open ? h : 0;
       }
-      __syncthreads();
+    } else if (tid == kSelThreads - 1) {
+      s_all = acc + hsum;
     }
-  }
-
-  // prefix of candidate lengths in rank order; thread t owns ranks [t*per2, (t+1)*per2)
-  const int per2 = (P + kSelThreads - 1) / kSelThreads;
-  const int r0 = tid * per2;
-  int my_cand = 0;
-  for (int i = 0; i < per2; ++i) {
-    const int r = r0 + i;
-    if (r < P && keys[r] != 0) my_cand += lens[(keys[r] - 1) & (kMaxUnits - 1)];
-  }
-  int ignored2;
-  int pre = block_exclusive_scan(my_cand, scr_i, &ignored2);
-  int my_sel = 0;
-  for (int i = 0; i < per2; ++i) {
-    const int r = r0 + i;
-    if (r < P && keys[r] != 0) {
-      const int u = static_cast<int>((keys[r] - 1) & (kMaxUnits - 1));
-      pre += lens[u];
-      if (pre <= cap_sel) {
-        chosen[u] = 1;
-        my_sel += lens[u];
+    __syncthreads();
+    const int cut = s_cut;
+    if (cut < 0) {                                  // every active candidate fits
+      taken = s_all;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (state[i] == 1) state[i] = 2;
+      break;
+    }
+    taken = s_taken;
+    const bool last = s_left <= 1 || lo == 0;       // one key left in the bucket: the misfit
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (state[i] == 1) {
+        const int dg = static_cast<int>((key[i] >> lo) & mask);
+        state[i] = dg > cut ? 2 : (dg < cut || last) ? 0 : 1;
       }
     }
+    if (last) break;
+    hi = lo;
   }
-  const int t_sel = block_sum(my_sel, scr_i);   // contains a barrier: chosen[] is complete
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     const int u = u0 + i;
-    if (i < per && u < U) keep_g[base + u] = (sys[i] || rec[i] || chosen[u]) ? 1 : 0;
+    if (i < per && u < U) keep_g[base + u] = (sys[i] || rec[i] || state[i] == 2) ? 1 : 0;
   }
-  if (tid == 0) kept_tokens_g[seg] = t_sys + t_rec + t_sel;
+  if (tid == 0) kept_tokens_g[seg] = t_sys + t_rec + taken;
 }
-
 
 // Single-wave variant for U <= 512 (every lane owns 8 consecutive units): the same plan with
 // wave-level scans (no workgroup barriers) and, instead of a full sort, an MSD radix select of

@@ -1,0 +1,57 @@
+"""Selection beyond 512 units (the workgroup radix select): unit counts at the edges of the
+units-per-thread steps, with candidate keys that agree in their high bits, are all equal, or span
+the whole key range, and budgets from nothing to everything, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_34653_amd import omnitide
+    omnitide.lib()
+    yield
+
+
+def _scores(kind, rng, U):
+    if kind == "clustered":                   # agree but for the low bits: first digit far down
+        return (1 << 41) + rng.integers(0, 700, size=U)
+    if kind == "equal":                       # ranked by unit id alone
+        return np.full(U, 12345)
+    return np.floor(2.0 ** rng.uniform(0, 49, size=U)).astype(np.int64)     # every key length
+
+
+@pytest.mark.parametrize("U", [513, 1024, 1025, 4096, 8191, 8192])
+@pytest.mark.parametrize("kind", ["clustered", "equal", "wide"])
+def test_wide_select_matches_oracle(U, kind):
+    from paper_2609_34653_amd import omnitide as ot
+    rng = np.random.default_rng(U + len(kind))
+    lens = rng.integers(0, 60, size=U)
+    end = np.cumsum(lens)
+    first = np.where(lens > 0, end - lens, 10 ** 7)
+    last = np.where(lens > 0, end - 1, -1)
+    wsum = _scores(kind, rng, U) * lens + rng.integers(0, np.maximum(lens, 1))
+    flags = (np.arange(U) == 0).astype(np.int64)
+    total, sysn = int(lens.sum()), int(lens[0])
+    up = lambda a, t=np.int32: torch.from_numpy(np.asarray(a, t)).cuda()   # noqa: E731
+    dev = (up(wsum, np.int64), up(lens), up(first), up(last), up(flags))
+    # nothing beyond the prefix, one candidate's worth, a part, all but one token, everything
+    for budget, recent in ((sysn, 0), (sysn + 25, 0), (total // 3, 300), (total - 1, 0),
+                           (total, total), (total, 100)):
+        sc = torch.full((U,), -7, dtype=torch.int64, device="cuda")
+        keep = torch.full((U,), 9, dtype=torch.uint8, device="cuda")
+        kept = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+        stat = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ot.omnitide_select_units(*dev, 1, U, budget, recent, sc, keep, kept, stat)
+        torch.cuda.synchronize()
+        assert int(stat.item()) == 0
+        score, want, n = oracle.select_units(wsum, lens, first, last, flags, budget, recent)
+        assert np.array_equal(sc.cpu().numpy(), score)
+        assert np.array_equal(keep.cpu().numpy(), want), (budget, recent)
+        assert int(kept.item()) == n
