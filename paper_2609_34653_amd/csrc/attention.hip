@@ -847,27 +847,44 @@ int span_attn_max_cap() { return 32768 * kKT; }
 
 namespace {
 
-// float32 -> bf16 (round to nearest even), four values per thread; n is a multiple of 4.
-__global__ __launch_bounds__(256) void cast_bf16_kernel(const float4* __restrict__ src,
-                                                        uint2* __restrict__ dst, size_t n4) {
-  for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n4;
+// float32 -> bf16 (round to nearest even) copies of q and of the rows of k and v in use, one
+// launch for the three: segment blockIdx.y's q, then its rows [0, n_ctx) of k, then of v, eight
+// values per thread and step.  Rows past n_ctx are never read by the attention kernel, so they
+// are not copied.  Bound by its launch at the sizes of a small model (11,003 of 12,288 rows of
+// 2 x 64 values and 331 x 14 x 64 of q, with three launches over all rows: 9.4 us).
+__global__ __launch_bounds__(256) void cast_qkv_kernel(
+    const float4* __restrict__ q, const float4* __restrict__ k, const float4* __restrict__ v,
+    u32x4* __restrict__ q16, u32x4* __restrict__ k16, u32x4* __restrict__ v16,
+    const int32_t* __restrict__ n_ctx_g, int cap, size_t q8, size_t row8) {
+  const int seg = blockIdx.y;
+  const size_t kv8 = static_cast<size_t>(min(max(n_ctx_g[seg], 0), cap)) * row8;
+  const size_t kv_base = static_cast<size_t>(seg) * cap * row8;
+  for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < q8 + 2 * kv8;
        i += static_cast<size_t>(gridDim.x) * 256) {
-    const float4 x = src[i];
-    const __bf16 b[4] = {static_cast<__bf16>(x.x), static_cast<__bf16>(x.y),
-                         static_cast<__bf16>(x.z), static_cast<__bf16>(x.w)};
-    dst[i] = make_uint2(static_cast<uint32_t>(__builtin_bit_cast(uint16_t, b[0])) |
-                            (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, b[1])) << 16),
-                        static_cast<uint32_t>(__builtin_bit_cast(uint16_t, b[2])) |
-                            (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, b[3])) << 16));
+    const bool is_q = i < q8, is_k = i < q8 + kv8;
+    const float4* src = is_q ? q : is_k ? k : v;
+    u32x4* dst = is_q ? q16 : is_k ? k16 : v16;
+    const size_t at = is_q ? seg * q8 + i : kv_base + (is_k ? i - q8 : i - q8 - kv8);
+    const float4 x = src[2 * at], y = src[2 * at + 1];
+    const bf16x8 b = {static_cast<__bf16>(x.x), static_cast<__bf16>(x.y),
+                      static_cast<__bf16>(x.z), static_cast<__bf16>(x.w),
+                      static_cast<__bf16>(y.x), static_cast<__bf16>(y.y),
+                      static_cast<__bf16>(y.z), static_cast<__bf16>(y.w)};
+    dst[at] = __builtin_bit_cast(u32x4, b);
   }
 }
 
-hipError_t cast_bf16(const void* src, void* dst, size_t n, hipStream_t stream) {
-  const size_t n4 = n / 4;
-  const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n4 + 255) / 256, 4096));
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(cast_bf16_kernel, dim3(blocks), dim3(256), 0, stream,
-                     static_cast<const float4*>(src), static_cast<uint2*>(dst), n4);
+hipError_t cast_qkv(const AttnArgs& a, void* q16, void* k16, void* v16, hipStream_t stream) {
+  const size_t q8 = static_cast<size_t>(a.chunk_len) * a.n_q_heads * a.head_dim / 8;
+  const size_t row8 = static_cast<size_t>(a.n_kv_heads) * a.head_dim / 8;
+  const size_t blocks = (q8 + 2 * a.cap * row8 + 255) / 256;
+  const unsigned grid_x = static_cast<unsigned>(
+      std::min<size_t>(blocks, std::max<size_t>(1, 8192 / static_cast<size_t>(a.n_seg))));
+  hipLaunchKernelGGL(cast_qkv_kernel, dim3(grid_x, a.n_seg), dim3(256), 0, stream,
+                     static_cast<const float4*>(a.q), static_cast<const float4*>(a.k),
+                     static_cast<const float4*>(a.v), static_cast<u32x4*>(q16),
+                     static_cast<u32x4*>(k16), static_cast<u32x4*>(v16), a.n_ctx, a.cap, q8,
+                     row8);
   return hipGetLastError();
 }
 
@@ -894,9 +911,7 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
     void* q16 = w;
     void* k16 = w + align256(nq * 2);
     void* v16 = w + align256(nq * 2) + align256(nkv * 2);
-    hipError_t e = cast_bf16(a.q, q16, nq, stream);
-    if (e == hipSuccess) e = cast_bf16(a.k, k16, nkv, stream);
-    if (e == hipSuccess) e = cast_bf16(a.v, v16, nkv, stream);
+    const hipError_t e = cast_qkv(a, q16, k16, v16, stream);
     if (e != hipSuccess) return e;
     b.q = q16;
     b.k = k16;

@@ -139,3 +139,29 @@ def test_output_and_input_dtypes(n_ctx, cap, L, Hq, Hkv, d):
     assert torch.equal(of, ref)
     ofb = run_attn_dtypes(q32, k32, v32, n_ctx, scale, torch.bfloat16)
     assert torch.equal(ofb.view(torch.int16), ob.view(torch.int16))
+
+
+def test_float32_rows_past_context_and_bad_segment():
+    """float32 inputs: rows past n_ctx (NaN here) take no part, and a segment whose n_ctx is out
+    of range is reported while the others are computed."""
+    from paper_2609_34653_amd import omnitide as ot
+    g = torch.Generator().manual_seed(5)
+    n_ctx, cap, L, Hq, Hkv, d = [65, 9000, 64, 127], 128, 33, 4, 2, 64
+    q = torch.randn(4, L, Hq, d, generator=g)
+    k, v = (torch.randn(4, cap, Hkv, d, generator=g) for _ in range(2))
+    for i, n in enumerate(n_ctx):
+        k[i, n:] = float("nan")
+        v[i, n:] = float("nan")
+    out = torch.full(q.shape, -3.0, device="cuda")
+    nb = ot.omnitide_attn_workspace_bytes(4, cap, L, Hq, Hkv, d, dtype=ot.F32)
+    ws = torch.full((nb,), 0xFF, dtype=torch.uint8, device="cuda")
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ot.omnitide_chunk_attn(q.cuda(), k.cuda(), v.cuda(), torch.tensor(n_ctx, dtype=torch.int32).cuda(),
+                           d ** -0.5, out, ws, st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == ot.E_CAPACITY
+    out = out.cpu()
+    assert bool((out[1] == -3.0).all())
+    for i in (0, 2, 3):
+        n = n_ctx[i]
+        check(out[i].numpy(), *(t[i].to(torch.bfloat16) for t in (q, k, v)), n, d ** -0.5)
