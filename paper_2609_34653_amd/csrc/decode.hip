@@ -468,11 +468,29 @@ hipError_t launch_decode_t(const DecodeArgs& a, int n_split, hipStream_t stream)
 
 }  // namespace
 
+// Splits per (segment, KV head).  One eight-wave workgroup is resident per CU, so the grid runs in
+// rounds of 256: a round costs its keys plus about 150 keys' worth of start, wave merge and drain,
+// the combine about 200 more.  The smallest s whose cost is within 5% of the least, from one full
+// round (256 / base) up to four times as many.  One round is right for few (segment, head)
+// pairs (one pair of 8 over 16,948 keys: 21.9 us with 32 splits, 27.0 with 43, 26.1 with 64), but
+// a base that leaves a round part-empty gains from more, smaller ones: 36 x 8 pairs over
+// 16,948 keys 602 us with one split (a second round of 32 workgroups), 423 with five; 24 x 8
+// over 9,173 keys 176 -> 169 with four; 20 x 8 over 5,000 keys 90 -> 87 with three.
 int decode_num_splits(int n_seg, int cap, int n_kv_heads) {
   const long base = static_cast<long>(n_kv_heads) * n_seg;
-  long s = kDecTargetWGs / base;
-  s = std::min(s, static_cast<long>((cap + 63) / 64));
-  return static_cast<int>(std::max(1L, std::min(s, 128L)));
+  const long most = std::max(1L, std::min(128L, (static_cast<long>(cap) + 63) / 64));
+  const long s0 = std::max(1L, std::min(kDecTargetWGs / base, most));
+  auto cost = [&](long s) {
+    const long rounds = (base * s + kDecTargetWGs - 1) / kDecTargetWGs;
+    return static_cast<double>(rounds) * (static_cast<double>(cap) / static_cast<double>(s) + 150.) +
+           (s > 1 ? 200. : 0.);
+  };
+  const long s1 = std::min(most, std::max(4 * s0, 8L));
+  double best = cost(s0);
+  for (long s = s0 + 1; s <= s1; ++s) best = std::min(best, cost(s));
+  long s = s0;
+  while (cost(s) > 1.05 * best) ++s;
+  return static_cast<int>(s);
 }
 
 size_t decode_workspace_bytes(int n_seg, int cap, int n_q, int n_q_heads, int n_kv_heads,

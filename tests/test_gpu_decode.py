@@ -117,3 +117,25 @@ def test_decode_workspace_reused_across_shapes():
         for s, n in enumerate(n_ctx):
             err = np.abs(got[s] - oracle_decode(q[s], k[s], v[s], n, d ** -0.5))
             assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, s, err.max())
+
+
+@pytest.mark.parametrize("n_seg,cap,n_q,Hq,Hkv,d,several", [
+    (33, 1500, 1, 16, 8, 64, True),     # just over one round of workgroups: split further
+    (20, 2500, 2, 16, 8, 128, True),    # a part-empty round
+    (33, 100, 1, 8, 8, 64, False),      # too short to split
+    (128, 700, 1, 4, 2, 64, False),     # exactly one round
+])
+def test_many_segments_split_counts(n_seg, cap, n_q, Hq, Hkv, d, several):
+    """Segments x KV heads around and past one round of workgroups, ragged contexts down to
+    n_q keys (empty splits)."""
+    from paper_2609_34653_amd import omnitide as ot
+    rng = np.random.default_rng(n_seg + cap)
+    n_ctx = [int(x) for x in rng.integers(n_q, cap + 1, size=n_seg)]
+    n_ctx[0], n_ctx[-1] = n_q, cap
+    nb = ot.omnitide_decode_workspace_bytes(n_seg, cap, n_q, Hq, Hkv, d)
+    assert (nb > 0) == several
+    q, k, v, out, status, scale = run_decode(n_ctx, cap, n_q, Hq, Hkv, d, seed=n_seg)
+    assert status == 0
+    for i in range(0, n_seg, 4):
+        err = np.abs(out[i] - oracle_decode(q[i], k[i], v[i], n_ctx[i], scale))
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, err.max(), err.mean())
