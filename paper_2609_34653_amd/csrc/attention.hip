@@ -43,7 +43,12 @@ constexpr int kAttnThreads = kAttnWaves * kWave;
 constexpr int kKT = 64;                  // keys per tile
 constexpr int kRowsWG = kAttnWaves * 32; // query rows per workgroup
 constexpr int kNumXcd = 8;
-constexpr int kTargetWGs = 512;          // two resident workgroups on each of 256 CUs
+constexpr int kNumCU = 256;
+constexpr long kMaxSplits = 16;          // key splits of a call at most
+// A call's split partials at most: two full row tiles per CU at d = 128.  They fit the fixed
+// scratch of the allocation-free call, so it takes every shape.
+constexpr double kMaxPartialBytes = 2. * kNumCU * kRowsWG * (128 + 2) * sizeof(float);
+static_assert(kMaxPartialBytes <= OMNITIDE_NOALLOC_SCRATCH_BYTES, "partials exceed the scratch");
 
 // LDS layout: two K and two V tile buffers, each row-major [64 keys][D]:
 //   K  16-byte chunks XOR-swizzled by kswz(key), so the 8 (and 16) lanes one LDS cycle serves
@@ -816,16 +821,40 @@ hipError_t launch_attn_t(const AttnArgs& a, int n_split, hipStream_t stream) {
 
 }  // namespace
 
+// Key splits of a call, by its estimated time in microseconds (d = 128; a tile of d = 64 takes 0.63
+// of one of d = 128).  A CU with one workgroup takes about 1.0 us per 64-key tile and with two
+// resident ones 0.85 per tile of each, and a workgroup's start and drain cost about two tiles
+// more; beyond 512 workgroups the grid runs in rounds.  Splitting adds the combine's launch and
+// the partials, written once and read once, and the output at about 8 TB/s together.  Measured over 22
+// shapes with rotating inputs the choice is 1.4% from the best split on average where filling 512
+// workgroups whatever the length was 5% (1,024 queries over 1,024 keys, 32/8 heads: 33.7 us with
+// two splits, 25.4 with one; 665 over 1,500: 34.4 with three, 32.4 with one; 89 over 601, 4/1 heads, d = 64:
+// 10.8 with two, 9.2 with ten).
 int attn_num_splits(int n_seg, int cap, int chunk_len, int n_q_heads, int n_kv_heads,
                     int head_dim) {
-  (void)head_dim;
   const int G = n_q_heads / n_kv_heads;
   const long n_mt = (static_cast<long>(chunk_len) * G + kRowsWG - 1) / kRowsWG;
   const long base = n_mt * n_kv_heads * n_seg;
-  const long tiles = (cap + kKT - 1) / kKT;
-  long s = kTargetWGs / base;
-  s = std::min(s, tiles / 4);
-  return static_cast<int>(std::max(1L, std::min(s, 16L)));
+  const long tiles = (static_cast<long>(cap) + kKT - 1) / kKT;
+  const double rows = static_cast<double>(n_seg) * chunk_len * n_q_heads;
+  const double part_bytes = rows * (head_dim + 2) * sizeof(float);    // of one split
+  const double tile_us = head_dim == 128 ? 1. : 0.63;
+  int best = 1;
+  double best_us = 0.;
+  for (long s = 1; s <= std::min<long>(tiles, kMaxSplits); ++s) {
+    if (s > 1 && static_cast<double>(s) * part_bytes > kMaxPartialBytes) break;
+    const long wgs = base * s;
+    const double per_tile = wgs <= kNumCU       ? 1.
+                            : wgs <= 2 * kNumCU ? 2 * 0.85
+                                                : 0.85 * ((wgs + kNumCU - 1) / kNumCU);
+    const double us = per_tile * tile_us * static_cast<double>((tiles + s - 1) / s + 2) +
+                      (s == 1 ? 0. : 3. + part_bytes * static_cast<double>(2 * s + 1) / 8e6);
+    if (s == 1 || us < best_us) {
+      best = static_cast<int>(s);
+      best_us = us;
+    }
+  }
+  return best;
 }
 
 size_t attn_workspace_bytes(int n_seg, int cap, int chunk_len, int n_q_heads, int n_kv_heads,
@@ -927,12 +956,6 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 // kernel (on the host it is only a stand-in for the symbol): the device address comes from
 // hipGetSymbolAddress, taken once per device with that device current, and is cached here.
 static __device__ __align__(256) uint8_t scratch[OMNITIDE_NOALLOC_SCRATCH_BYTES];
-// Splits times row-tile workgroups never exceed kTargetWGs and a row tile holds kRowsWG rows, so
-// the partials need at most kTargetWGs * kRowsWG * (128 + 2) floats: every valid shape fits.
-static_assert(static_cast<size_t>(kTargetWGs) * kRowsWG * (128 + 2) * sizeof(float) <=
-                  OMNITIDE_NOALLOC_SCRATCH_BYTES,
-              "the split heuristic can exceed the fixed scratch");
-
 namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

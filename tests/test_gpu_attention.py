@@ -165,3 +165,21 @@ def test_float32_rows_past_context_and_bad_segment():
     for i in (0, 2, 3):
         n = n_ctx[i]
         check(out[i].numpy(), *(t[i].to(torch.bfloat16) for t in (q, k, v)), n, d ** -0.5)
+
+
+@pytest.mark.parametrize("n_ctx,cap,L,Hq,Hkv,d", [
+    ([601], 601, 89, 4, 1, 64),           # one or two tiles per split
+    ([100], 4000, 64, 8, 1, 128),         # the context ends in the first splits: the rest are empty
+    ([1024], 1024, 1024, 8, 8, 64),       # no history, unsplit
+    ([64, 2000], 2100, 33, 8, 2, 128),    # a one-tile segment beside a long one
+])
+def test_split_choice_edges(n_ctx, cap, L, Hq, Hkv, d):
+    """Splits of one tile, empty splits and unsplit calls, with a NaN-filled workspace."""
+    rng = np.random.default_rng(cap + L)
+    n_seg = len(n_ctx)
+    q = bf16(rng.standard_normal((n_seg, L, Hq, d)))
+    k, v = (bf16(rng.standard_normal((n_seg, cap, Hkv, d))) for _ in range(2))
+    out, status = run_attn(q, k, v, n_ctx, d ** -0.5)
+    assert status == 0
+    for i, n in enumerate(n_ctx):
+        check(out[i], q[i], k[i], v[i], n, d ** -0.5)
