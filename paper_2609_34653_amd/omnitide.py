@@ -138,13 +138,14 @@ def version() -> str:
 
 # ----------------------------------------------------------------------------- marshalling
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
+# A call checks and passes up to 30 tensors, so the common case (a plain contiguous device tensor of
+# the right type and size) takes one short function per tensor that returns the address; anything
+# else goes through _need, which raises or accepts it.  Four calls' marshalling bounds a small step:
+# the 1.6K-token float32 step took 64 us with separate checks and pointer objects, 49 us so.
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
@@ -166,6 +167,37 @@ def _check(code: int, where: str):
         raise OmnitideError(code, where)
 
 
+_T, _BF16, _F32, _I32, _I64, _U8 = (torch.Tensor, torch.bfloat16, torch.float32, torch.int32,
+                                    torch.int64, torch.uint8)
+
+
+def _dev(t, name: str, dtype: torch.dtype, numel: int) -> int:
+    """Address of a contiguous device tensor of `dtype` and `numel` elements."""
+    if not (type(t) is _T and t.dtype is dtype and t.is_cuda and t.is_contiguous()
+            and t.numel() == numel):
+        _need(t, name, (dtype,), numel)
+    return t.data_ptr()
+
+
+def _buf(t, name: str = "workspace") -> int:
+    """Address of a uint8 device buffer of any size."""
+    if not (type(t) is _T and t.dtype is _U8 and t.is_cuda and t.is_contiguous()):
+        _need(t, name, (_U8,))
+    return t.data_ptr()
+
+
+def _pool(t, name: str) -> int:
+    """Address of a bf16 or float32 device tensor."""
+    if not (type(t) is _T and (t.dtype is _BF16 or t.dtype is _F32) and t.is_cuda
+            and t.is_contiguous()):
+        _need(t, name, (_BF16, _F32))
+    return t.data_ptr()
+
+
+def _status(t) -> Optional[int]:
+    return None if t is None else _dev(t, "d_status", _I32, 1)
+
+
 def _pool_dims(t: torch.Tensor, name: str):
     """[n_seg, n_slots, H, d] (or [n_slots, H, d] = one segment)."""
     if t.dim() == 3:
@@ -179,48 +211,33 @@ def _kv_dtype(t: torch.Tensor) -> int:
     return BF16 if t.dtype == torch.bfloat16 else F32
 
 
-I64, I32, U8 = (torch.int64,), (torch.int32,), (torch.uint8,)
+_F4 = ctypes.c_float * 4
 
 
 def omnitide_score_units(k, unit_id, modality, weights, n_units, unit_wsum, unit_len,
                          unit_first_slot, unit_last_slot, unit_flags, d_status=None, stream=None):
     n_seg, n_slots, H, d = _pool_dims(k, "k")
-    _need(k, "k", (torch.bfloat16, torch.float32))
-    _need(unit_id, "unit_id", I32, n_seg * n_slots)
-    _need(modality, "modality", U8, n_seg * n_slots)
-    nu = n_seg * n_units
-    _need(unit_wsum, "unit_wsum", I64, nu)
-    for t, nm in ((unit_len, "unit_len"), (unit_first_slot, "unit_first_slot"),
-                  (unit_last_slot, "unit_last_slot"), (unit_flags, "unit_flags")):
-        _need(t, nm, I32, nu)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    w = (ctypes.c_float * 4)(*[float(x) for x in weights])
-    _check(lib().omnitide_score_units(_ptr(k), _kv_dtype(k), n_seg, n_slots, H, d,
-                                      _ptr(unit_id), _ptr(modality), ctypes.cast(w, _P), n_units,
-                                      _ptr(unit_wsum), _ptr(unit_len), _ptr(unit_first_slot),
-                                      _ptr(unit_last_slot), _ptr(unit_flags), _ptr(d_status),
-                                      _stream(stream)), "omnitide_score_units")
+    ns, nu = n_seg * n_slots, n_seg * n_units
+    args = (_pool(k, "k"), _kv_dtype(k), n_seg, n_slots, H, d, _dev(unit_id, "unit_id", _I32, ns),
+            _dev(modality, "modality", _U8, ns), _F4(*[float(x) for x in weights]), n_units,
+            _dev(unit_wsum, "unit_wsum", _I64, nu), _dev(unit_len, "unit_len", _I32, nu),
+            _dev(unit_first_slot, "unit_first_slot", _I32, nu),
+            _dev(unit_last_slot, "unit_last_slot", _I32, nu),
+            _dev(unit_flags, "unit_flags", _I32, nu), _status(d_status))
+    _check(lib().omnitide_score_units(*args, _stream(stream)), "omnitide_score_units")
 
 
 def omnitide_select_units(unit_wsum, unit_len, unit_first_slot, unit_last_slot, unit_flags,
                           n_seg, n_units, budget_tokens, recent_tokens, unit_score, keep,
                           kept_tokens, d_status=None, stream=None):
     nu = n_seg * n_units
-    _need(unit_wsum, "unit_wsum", I64, nu)
-    for t, nm in ((unit_len, "unit_len"), (unit_first_slot, "unit_first_slot"),
-                  (unit_last_slot, "unit_last_slot"), (unit_flags, "unit_flags")):
-        _need(t, nm, I32, nu)
-    _need(unit_score, "unit_score", I64, nu)
-    _need(keep, "keep", U8, nu)
-    _need(kept_tokens, "kept_tokens", I32, n_seg)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_select_units(_ptr(unit_wsum), _ptr(unit_len), _ptr(unit_first_slot),
-                                       _ptr(unit_last_slot), _ptr(unit_flags), n_seg, n_units,
-                                       budget_tokens, recent_tokens, _ptr(unit_score), _ptr(keep),
-                                       _ptr(kept_tokens), _ptr(d_status), _stream(stream)),
-           "omnitide_select_units")
+    args = (_dev(unit_wsum, "unit_wsum", _I64, nu), _dev(unit_len, "unit_len", _I32, nu),
+            _dev(unit_first_slot, "unit_first_slot", _I32, nu),
+            _dev(unit_last_slot, "unit_last_slot", _I32, nu),
+            _dev(unit_flags, "unit_flags", _I32, nu), n_seg, n_units, budget_tokens,
+            recent_tokens, _dev(unit_score, "unit_score", _I64, nu), _dev(keep, "keep", _U8, nu),
+            _dev(kept_tokens, "kept_tokens", _I32, n_seg), _status(d_status))
+    _check(lib().omnitide_select_units(*args, _stream(stream)), "omnitide_select_units")
 
 
 def omnitide_plan_spans_workspace_bytes(n_seg, n_slots, n_units) -> int:
@@ -231,26 +248,17 @@ def omnitide_plan_spans(unit_len, unit_first_slot, unit_last_slot, unit_flags, u
                         n_seg, n_slots, n_units, low_watermark, high_watermark, recent_tokens,
                         sink_video, sink_audio, text_budget, keep_len, keep_slot, kept_tokens,
                         workspace, d_status=None, stream=None):
-    nu = n_seg * n_units
-    for t, nm in ((unit_len, "unit_len"), (unit_first_slot, "unit_first_slot"),
-                  (unit_last_slot, "unit_last_slot"), (unit_flags, "unit_flags"),
-                  (keep_len, "keep_len")):
-        _need(t, nm, I32, nu)
-    _need(unit_id, "unit_id", I32, n_seg * n_slots)
-    _need(modality, "modality", U8, n_seg * n_slots)
-    _need(keep_slot, "keep_slot", U8, n_seg * n_slots)
-    _need(kept_tokens, "kept_tokens", I32, n_seg)
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_plan_spans(_ptr(unit_len), _ptr(unit_first_slot), _ptr(unit_last_slot),
-                                     _ptr(unit_flags), _ptr(unit_id), _ptr(modality), n_seg,
-                                     n_slots, n_units, low_watermark, high_watermark,
-                                     recent_tokens, sink_video, sink_audio, text_budget,
-                                     _ptr(keep_len), _ptr(keep_slot), _ptr(kept_tokens),
-                                     _ptr(workspace), workspace.numel(), _ptr(d_status),
-                                     _stream(stream)),
-           "omnitide_plan_spans")
+    nu, ns = n_seg * n_units, n_seg * n_slots
+    args = (_dev(unit_len, "unit_len", _I32, nu),
+            _dev(unit_first_slot, "unit_first_slot", _I32, nu),
+            _dev(unit_last_slot, "unit_last_slot", _I32, nu),
+            _dev(unit_flags, "unit_flags", _I32, nu), _dev(unit_id, "unit_id", _I32, ns),
+            _dev(modality, "modality", _U8, ns), n_seg, n_slots, n_units, low_watermark,
+            high_watermark, recent_tokens, sink_video, sink_audio, text_budget,
+            _dev(keep_len, "keep_len", _I32, nu), _dev(keep_slot, "keep_slot", _U8, ns),
+            _dev(kept_tokens, "kept_tokens", _I32, n_seg), _buf(workspace), workspace.numel(),
+            _status(d_status))
+    _check(lib().omnitide_plan_spans(*args, _stream(stream)), "omnitide_plan_spans")
 
 
 def omnitide_compact_workspace_bytes(n_seg, n_units, cap_dst) -> int:
@@ -261,49 +269,41 @@ def _compact_call_args(k_src, v_src, page_size, unit_id_src, modality_src, pos_s
                        unit_len, unit_first_slot, n_units, k_chunk, v_chunk, chunk_modality,
                        chunk_unit, k_dst, v_dst, unit_id_dst, modality_dst, pos_dst, src_of_dst,
                        unit_remap, n_ctx, n_pages, workspace, d_status, per_slot=False):
-    """Checked C arguments shared by the compaction entry points (all but the rotary arguments
-    and the stream).  `keep` is the uint8 keep flags per unit, or (per_slot) the span plan's
-    uint8 keep mask per slot."""
+    """Checked C arguments shared by the compaction entry points (all but the rotary arguments,
+    the status and the stream).  `keep` is the uint8 keep flags per unit, or (per_slot) the span
+    plan's uint8 keep mask per slot."""
     n_seg, n_slots, H, d = _pool_dims(k_src, "k_src")
-    dt = (k_src.dtype,)
-    _need(k_src, "k_src", (torch.bfloat16, torch.float32))
-    _need(v_src, "v_src", dt, k_src.numel())
-    ns = n_seg * n_slots
-    _need(unit_id_src, "unit_id_src", I32, ns)
-    _need(modality_src, "modality_src", U8, ns)
-    _need(pos_src, "pos_src", I32, ns)
-    nu = n_seg * n_units
-    _need(keep, "keep_slot" if per_slot else "keep", U8, ns if per_slot else nu)
-    _need(unit_len, "unit_len", I32, nu)
-    _need(unit_first_slot, "unit_first_slot", I32, nu)
+    dt = k_src.dtype
+    ks = _pool(k_src, "k_src")
+    vs = _dev(v_src, "v_src", dt, k_src.numel())
+    ns, nu = n_seg * n_slots, n_seg * n_units
+    src = (_dev(unit_id_src, "unit_id_src", _I32, ns), _dev(modality_src, "modality_src", _U8, ns),
+           _dev(pos_src, "pos_src", _I32, ns),
+           _dev(keep, "keep_slot", _U8, ns) if per_slot else _dev(keep, "keep", _U8, nu),
+           _dev(unit_len, "unit_len", _I32, nu),
+           _dev(unit_first_slot, "unit_first_slot", _I32, nu))
     L = 0 if chunk_modality is None else chunk_modality.numel()
     if L:
-        _need(k_chunk, "k_chunk", dt, n_seg * L * H * d)
-        _need(v_chunk, "v_chunk", dt, n_seg * L * H * d)
-        _need(chunk_modality, "chunk_modality", U8, L)
-        _need(chunk_unit, "chunk_unit", I32, L)
+        nc = n_seg * L * H * d
+        chunk = (_dev(k_chunk, "k_chunk", dt, nc), _dev(v_chunk, "v_chunk", dt, nc),
+                 _dev(chunk_modality, "chunk_modality", _U8, L),
+                 _dev(chunk_unit, "chunk_unit", _I32, L))
+    else:
+        chunk = tuple(None if t is None else t.data_ptr()
+                      for t in (k_chunk, v_chunk, chunk_modality, chunk_unit))
     ds, cap, Hd, dd = _pool_dims(k_dst, "k_dst")
     if ds != n_seg or Hd != H or dd != d:
         raise ValueError("k_dst shape does not match k_src")
-    _need(k_dst, "k_dst", dt)
-    _need(v_dst, "v_dst", dt, k_dst.numel())
     nd = n_seg * cap
-    _need(unit_id_dst, "unit_id_dst", I32, nd)
-    _need(modality_dst, "modality_dst", U8, nd)
-    _need(pos_dst, "pos_dst", I32, nd)
-    _need(src_of_dst, "src_of_dst", I32, nd)
-    _need(unit_remap, "unit_remap", I32, nu)
-    _need(n_ctx, "n_ctx", I32, n_seg)
-    _need(n_pages, "n_pages", I32, n_seg)
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    return (_ptr(k_src), _ptr(v_src), _kv_dtype(k_src), n_seg, n_slots, H, d, page_size,
-            _ptr(unit_id_src), _ptr(modality_src), _ptr(pos_src), _ptr(keep), _ptr(unit_len),
-            _ptr(unit_first_slot), n_units, _ptr(k_chunk), _ptr(v_chunk), _ptr(chunk_modality),
-            _ptr(chunk_unit), L, _ptr(k_dst), _ptr(v_dst), cap, _ptr(unit_id_dst),
-            _ptr(modality_dst), _ptr(pos_dst), _ptr(src_of_dst), _ptr(unit_remap), _ptr(n_ctx),
-            _ptr(n_pages), _ptr(workspace), workspace.numel())
+    if k_dst.dtype is not dt or not k_dst.is_cuda or not k_dst.is_contiguous():
+        _need(k_dst, "k_dst", (dt,))
+    return (ks, vs, _kv_dtype(k_src), n_seg, n_slots, H, d, page_size, *src, n_units, *chunk, L,
+            k_dst.data_ptr(), _dev(v_dst, "v_dst", dt, k_dst.numel()), cap,
+            _dev(unit_id_dst, "unit_id_dst", _I32, nd),
+            _dev(modality_dst, "modality_dst", _U8, nd), _dev(pos_dst, "pos_dst", _I32, nd),
+            _dev(src_of_dst, "src_of_dst", _I32, nd), _dev(unit_remap, "unit_remap", _I32, nu),
+            _dev(n_ctx, "n_ctx", _I32, n_seg), _dev(n_pages, "n_pages", _I32, n_seg),
+            _buf(workspace), workspace.numel())
 
 
 def omnitide_compact_kv(k_src, v_src, page_size, unit_id_src, modality_src, pos_src, keep,
@@ -315,7 +315,7 @@ def omnitide_compact_kv(k_src, v_src, page_size, unit_id_src, modality_src, pos_
                               chunk_modality, chunk_unit, k_dst, v_dst, unit_id_dst,
                               modality_dst, pos_dst, src_of_dst, unit_remap, n_ctx, n_pages,
                               workspace, d_status)
-    _check(lib().omnitide_compact_kv(*args, _ptr(d_status), _stream(stream)),
+    _check(lib().omnitide_compact_kv(*args, _status(d_status), _stream(stream)),
            "omnitide_compact_kv")
 
 
@@ -331,7 +331,7 @@ def omnitide_compact_kv_rope(k_src, v_src, page_size, unit_id_src, modality_src,
                               modality_dst, pos_dst, src_of_dst, unit_remap, n_ctx, n_pages,
                               workspace, d_status)
     _check(lib().omnitide_compact_kv_rope(*args, float(rope_base), int(rope_dims),
-                                          int(rope_style), _ptr(d_status), _stream(stream)),
+                                          int(rope_style), _status(d_status), _stream(stream)),
            "omnitide_compact_kv_rope")
 
 
@@ -347,7 +347,7 @@ def omnitide_compact_kv_spans(k_src, v_src, page_size, unit_id_src, modality_src
                               modality_dst, pos_dst, src_of_dst, unit_remap, n_ctx, n_pages,
                               workspace, d_status, per_slot=True)
     _check(lib().omnitide_compact_kv_spans(*args, float(rope_base), int(rope_dims),
-                                           int(rope_style), _ptr(d_status), _stream(stream)),
+                                           int(rope_style), _status(d_status), _stream(stream)),
            "omnitide_compact_kv_spans")
 
 
@@ -357,8 +357,9 @@ def omnitide_attn_workspace_bytes(n_seg, cap, chunk_len, n_q_heads, n_kv_heads, 
                                                    n_kv_heads, head_dim))
 
 
-def omnitide_chunk_attn(q, k, v, n_ctx, scale, out, workspace=None, d_status=None, stream=None):
-    """q/k/v bf16 or float32 (all the same); out float32 or bf16 (its dtype selects)."""
+def _q_dims(q, k):
+    """(n_seg, tokens, query heads, d, cap, KV heads) of q [n_seg, L, Hq, d] (or [L, Hq, d]) and
+    its pool."""
     if q.dim() == 3:
         n_seg, (L, Hq, d) = 1, q.shape
     else:
@@ -366,47 +367,54 @@ def omnitide_chunk_attn(q, k, v, n_ctx, scale, out, workspace=None, d_status=Non
     ds, cap, Hkv, dd = _pool_dims(k, "k")
     if ds != n_seg or dd != d:
         raise ValueError("k shape does not match q")
-    _need(q, "q", (torch.bfloat16, torch.float32))
-    _need(k, "k", (q.dtype,))
-    _need(v, "v", (q.dtype,), k.numel())
-    _need(n_ctx, "n_ctx", I32, n_seg)
-    _need(out, "out", (torch.float32, torch.bfloat16), q.numel())
-    if workspace is not None:
-        _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_chunk_attn(_ptr(q), _ptr(k), _ptr(v), _kv_dtype(q), _ptr(n_ctx), n_seg,
-                                     cap, L, Hq, Hkv, d, float(scale), _ptr(out), _kv_dtype(out),
-                                     _ptr(workspace),
-                                     0 if workspace is None else workspace.numel(),
-                                     _ptr(d_status), _stream(stream)), "omnitide_chunk_attn")
+    return n_seg, L, Hq, d, cap, Hkv
+
+
+def _out(out, numel) -> int:
+    """Address of a float32 or bf16 output."""
+    if not (type(out) is _T and (out.dtype is _F32 or out.dtype is _BF16) and out.is_cuda
+            and out.is_contiguous() and out.numel() == numel):
+        _need(out, "out", (_F32, _BF16), numel)
+    return out.data_ptr()
+
+
+def omnitide_chunk_attn(q, k, v, n_ctx, scale, out, workspace=None, d_status=None, stream=None):
+    """q/k/v bf16 or float32 (all the same); out float32 or bf16 (its dtype selects)."""
+    n_seg, L, Hq, d, cap, Hkv = _q_dims(q, k)
+    args = (_pool(q, "q"), _dev(k, "k", q.dtype, k.numel()), _dev(v, "v", q.dtype, k.numel()),
+            _kv_dtype(q), _dev(n_ctx, "n_ctx", _I32, n_seg), n_seg, cap, L, Hq, Hkv, d,
+            float(scale), _out(out, q.numel()), _kv_dtype(out),
+            None if workspace is None else _buf(workspace),
+            0 if workspace is None else workspace.numel(), _status(d_status))
+    _check(lib().omnitide_chunk_attn(*args, _stream(stream)), "omnitide_chunk_attn")
 
 
 def omnitide_chunk_attn_noalloc(q, k, v, n_ctx, scale, out, d_status=None, stream=None):
     """omnitide_chunk_attn with the library's fixed scratch (allocates nothing)."""
-    if q.dim() == 3:
-        n_seg, (L, Hq, d) = 1, q.shape
-    else:
-        n_seg, L, Hq, d = q.shape
-    ds, cap, Hkv, dd = _pool_dims(k, "k")
-    if ds != n_seg or dd != d:
-        raise ValueError("k shape does not match q")
-    _need(q, "q", (torch.bfloat16,))
-    _need(k, "k", (torch.bfloat16,))
-    _need(v, "v", (torch.bfloat16,), k.numel())
-    _need(n_ctx, "n_ctx", I32, n_seg)
-    _need(out, "out", (torch.float32, torch.bfloat16), q.numel())
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_chunk_attn_noalloc(_ptr(q), _ptr(k), _ptr(v), _ptr(n_ctx), n_seg, cap,
-                                             L, Hq, Hkv, d, float(scale), _ptr(out),
-                                             _kv_dtype(out), _ptr(d_status), _stream(stream)),
+    n_seg, L, Hq, d, cap, Hkv = _q_dims(q, k)
+    args = (_dev(q, "q", _BF16, q.numel()), _dev(k, "k", _BF16, k.numel()),
+            _dev(v, "v", _BF16, k.numel()), _dev(n_ctx, "n_ctx", _I32, n_seg), n_seg, cap, L, Hq,
+            Hkv, d, float(scale), _out(out, q.numel()), _kv_dtype(out), _status(d_status))
+    _check(lib().omnitide_chunk_attn_noalloc(*args, _stream(stream)),
            "omnitide_chunk_attn_noalloc")
+
 
 def omnitide_span_attn_workspace_bytes(n_seg, cap, chunk_len, n_q_heads, n_kv_heads,
                                        head_dim) -> int:
     return int(lib().omnitide_span_attn_workspace_bytes(n_seg, cap, chunk_len, n_q_heads,
                                                         n_kv_heads, head_dim))
+
+
+def _span_call_args(q, k, v, key_pos, span, q_pos0, scale, out, workspace, d_status,
+                    skip_empty_tiles, position_order):
+    """Checked C arguments of the two calls over a pool with holes (all but the stream)."""
+    n_seg, L, Hq, d, cap, Hkv = _q_dims(q, k)
+    return (_dev(q, "q", _BF16, q.numel()), _dev(k, "k", _BF16, k.numel()),
+            _dev(v, "v", _BF16, k.numel()), _dev(key_pos, "key_pos", _I32, n_seg * cap),
+            _dev(span, "span", _I32, n_seg), _dev(q_pos0, "q_pos0", _I32, n_seg), n_seg, cap, L,
+            Hq, Hkv, d, float(scale), 2 if position_order else 1 if skip_empty_tiles else 0,
+            _dev(out, "out", _F32, q.numel()), _buf(workspace), workspace.numel(),
+            _status(d_status))
 
 
 def omnitide_span_attn(q, k, v, key_pos, span, q_pos0, scale, out, workspace, d_status=None,
@@ -416,29 +424,9 @@ def omnitide_span_attn(q, k, v, key_pos, span, q_pos0, scale, out, workspace, d_
     Traversal: position_order (the entries gathered in position order; they must hold the
     positions 0 .. q_pos0 + L - 1 once each), else tile skipping if skip_empty_tiles, else the
     full span."""
-    if q.dim() == 3:
-        n_seg, (L, Hq, d) = 1, q.shape
-    else:
-        n_seg, L, Hq, d = q.shape
-    ds, cap, Hkv, dd = _pool_dims(k, "k")
-    if ds != n_seg or dd != d:
-        raise ValueError("k shape does not match q")
-    _need(q, "q", (torch.bfloat16,))
-    _need(k, "k", (torch.bfloat16,))
-    _need(v, "v", (torch.bfloat16,), k.numel())
-    _need(key_pos, "key_pos", I32, n_seg * cap)
-    _need(span, "span", I32, n_seg)
-    _need(q_pos0, "q_pos0", I32, n_seg)
-    _need(out, "out", (torch.float32,), q.numel())
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_span_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(key_pos), _ptr(span),
-                                    _ptr(q_pos0), n_seg, cap, L, Hq, Hkv, d, float(scale),
-                                    2 if position_order else 1 if skip_empty_tiles else 0,
-                                    _ptr(out), _ptr(workspace),
-                                    workspace.numel(),
-                                    _ptr(d_status), _stream(stream)), "omnitide_span_attn")
+    args = _span_call_args(q, k, v, key_pos, span, q_pos0, scale, out, workspace, d_status,
+                           skip_empty_tiles, position_order)
+    _check(lib().omnitide_span_attn(*args, _stream(stream)), "omnitide_span_attn")
 
 
 def omnitide_decode_span_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads,
@@ -453,62 +441,37 @@ def omnitide_decode_span_attn(q, k, v, key_pos, span, q_pos0, scale, out, worksp
     """Decode attention of n_q tokens over a pool with holes: q [n_seg, n_q, Hq, d] bf16;
     k/v [n_seg, cap, Hkv, d] bf16; key_pos int32 [n_seg * cap] (-1 = empty slot); span, q_pos0
     int32 [n_seg] (device); out float32 like q.  Traversal as omnitide_span_attn."""
-    if q.dim() == 3:
-        n_seg, (nq, Hq, d) = 1, q.shape
-    else:
-        n_seg, nq, Hq, d = q.shape
-    ds, cap, Hkv, dd = _pool_dims(k, "k")
-    if ds != n_seg or dd != d:
-        raise ValueError("k shape does not match q")
-    _need(q, "q", (torch.bfloat16,))
-    _need(k, "k", (torch.bfloat16,))
-    _need(v, "v", (torch.bfloat16,), k.numel())
-    _need(key_pos, "key_pos", I32, n_seg * cap)
-    _need(span, "span", I32, n_seg)
-    _need(q_pos0, "q_pos0", I32, n_seg)
-    _need(out, "out", (torch.float32,), q.numel())
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_decode_span_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(key_pos), _ptr(span),
-                                           _ptr(q_pos0), n_seg, cap, nq, Hq, Hkv, d,
-                                           float(scale),
-                                           2 if position_order else 1 if skip_empty_tiles else 0,
-                                           _ptr(out),
-                                           _ptr(workspace), workspace.numel(), _ptr(d_status),
-                                           _stream(stream)), "omnitide_decode_span_attn")
+    args = _span_call_args(q, k, v, key_pos, span, q_pos0, scale, out, workspace, d_status,
+                           skip_empty_tiles, position_order)
+    _check(lib().omnitide_decode_span_attn(*args, _stream(stream)), "omnitide_decode_span_attn")
 
 
 def omnitide_evict_native_workspace_bytes(n_seg, n_units) -> int:
     return int(lib().omnitide_evict_native_workspace_bytes(n_seg, n_units))
 
 
+def _evict_call_args(unit_id, pos, n_seg, n_units, unit_len, keep, keep_len):
+    """Checked (unit_id, pos, keep, keep_len, unit_len) addresses and cap of an eviction."""
+    cap = unit_id.numel() // n_seg
+    nu = n_seg * n_units
+    head = (_dev(unit_id, "unit_id", _I32, n_seg * cap), _dev(pos, "pos", _I32, n_seg * cap))
+    if keep_len is not None:
+        plan = (None, _dev(keep_len, "keep_len", _I32, nu))
+    else:
+        plan = (_dev(keep, "keep", _U8, nu), None)
+    return cap, nu, (*head, *plan, _dev(unit_len, "unit_len", _I32, nu))
+
+
 def omnitide_evict_native(unit_id, pos, n_seg, n_units, unit_len, unit_remap, kept_tokens,
                           n_kept_units, span, workspace, keep=None, keep_len=None,
                           d_status=None, stream=None):
     """Logical eviction in place of the tags unit_id / pos ([n_seg * cap] int32)."""
-    cap = unit_id.numel() // n_seg
-    nu = n_seg * n_units
-    _need(unit_id, "unit_id", I32, n_seg * cap)
-    _need(pos, "pos", I32, n_seg * cap)
-    if keep_len is not None:
-        _need(keep_len, "keep_len", I32, nu)
-    else:
-        _need(keep, "keep", U8, nu)
-    for t, nm in ((unit_len, "unit_len"), (unit_remap, "unit_remap")):
-        _need(t, nm, I32, nu)
-    for t, nm in ((kept_tokens, "kept_tokens"), (n_kept_units, "n_kept_units"), (span, "span")):
-        _need(t, nm, I32, n_seg)
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_evict_native(n_seg, cap, _ptr(unit_id), _ptr(pos),
-                                       _ptr(keep) if keep_len is None else None, _ptr(keep_len),
-                                       _ptr(unit_len), n_units, _ptr(unit_remap),
-                                       _ptr(kept_tokens), _ptr(n_kept_units), _ptr(span),
-                                       _ptr(workspace), workspace.numel(), _ptr(d_status),
-                                       _stream(stream)), "omnitide_evict_native")
-
+    cap, nu, head = _evict_call_args(unit_id, pos, n_seg, n_units, unit_len, keep, keep_len)
+    args = (n_seg, cap, *head, n_units, _dev(unit_remap, "unit_remap", _I32, nu),
+            _dev(kept_tokens, "kept_tokens", _I32, n_seg),
+            _dev(n_kept_units, "n_kept_units", _I32, n_seg), _dev(span, "span", _I32, n_seg),
+            _buf(workspace), workspace.numel(), _status(d_status))
+    _check(lib().omnitide_evict_native(*args, _stream(stream)), "omnitide_evict_native")
 
 
 def omnitide_evict_native_rope_workspace_bytes(n_seg, n_units, cap) -> int:
@@ -521,33 +484,19 @@ def omnitide_evict_native_rope(unit_id, pos, k, n_seg, n_units, unit_len, unit_r
                                stream=None):
     """Logical eviction in place plus the rotary adjustment, in place, of the keys k
     ([n_seg, cap, H, d] bf16 or float32) whose positions shift."""
-    cap = unit_id.numel() // n_seg
-    nu = n_seg * n_units
     ds, kcap, H, d = _pool_dims(k, "k")
-    if ds != n_seg or kcap != cap:
+    if ds != n_seg or kcap != unit_id.numel() // n_seg:
         raise ValueError("k shape does not match the tags")
-    _need(k, "k", (torch.bfloat16, torch.float32))
-    _need(unit_id, "unit_id", I32, n_seg * cap)
-    _need(pos, "pos", I32, n_seg * cap)
-    if keep_len is not None:
-        _need(keep_len, "keep_len", I32, nu)
-    else:
-        _need(keep, "keep", U8, nu)
-    for t, nm in ((unit_len, "unit_len"), (unit_remap, "unit_remap")):
-        _need(t, nm, I32, nu)
-    for t, nm in ((kept_tokens, "kept_tokens"), (n_kept_units, "n_kept_units"), (span, "span")):
-        _need(t, nm, I32, n_seg)
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_evict_native_rope(n_seg, cap, _ptr(unit_id), _ptr(pos),
-                                            _ptr(keep) if keep_len is None else None,
-                                            _ptr(keep_len), _ptr(unit_len), n_units, _ptr(k),
-                                            _kv_dtype(k), H, d, float(rope_base), int(rope_dims),
-                                            int(rope_style), _ptr(unit_remap), _ptr(kept_tokens),
-                                            _ptr(n_kept_units), _ptr(span), _ptr(workspace),
-                                            workspace.numel(), _ptr(d_status), _stream(stream)),
+    kp = _pool(k, "k")
+    cap, nu, head = _evict_call_args(unit_id, pos, n_seg, n_units, unit_len, keep, keep_len)
+    args = (n_seg, cap, *head, n_units, kp, _kv_dtype(k), H, d, float(rope_base), int(rope_dims),
+            int(rope_style), _dev(unit_remap, "unit_remap", _I32, nu),
+            _dev(kept_tokens, "kept_tokens", _I32, n_seg),
+            _dev(n_kept_units, "n_kept_units", _I32, n_seg), _dev(span, "span", _I32, n_seg),
+            _buf(workspace), workspace.numel(), _status(d_status))
+    _check(lib().omnitide_evict_native_rope(*args, _stream(stream)),
            "omnitide_evict_native_rope")
+
 
 def omnitide_pack_suffix_workspace_bytes(dtype, n_seg, cap, n_kv_heads, head_dim) -> int:
     return int(lib().omnitide_pack_suffix_workspace_bytes(dtype, n_seg, cap, n_kv_heads,
@@ -558,19 +507,13 @@ def omnitide_pack_suffix(k, v, page_size, min_pages, unit_id, modality, pos, spa
                          workspace, stream=None):
     """Ordered-suffix packing in place of pools k/v [n_seg, cap, H, d] and their tags."""
     n_seg, cap, H, d = _pool_dims(k, "k")
-    _need(k, "k", (torch.bfloat16, torch.float32))
-    _need(v, "v", (k.dtype,), k.numel())
-    _need(unit_id, "unit_id", I32, n_seg * cap)
-    _need(modality, "modality", U8, n_seg * cap)
-    _need(pos, "pos", I32, n_seg * cap)
-    for t, nm in ((span, "span"), (cut, "cut"), (moved, "moved")):
-        _need(t, nm, I32, n_seg)
-    _need(workspace, "workspace", U8)
-    _check(lib().omnitide_pack_suffix(_ptr(k), _ptr(v), _kv_dtype(k), n_seg, cap, H, d,
-                                      page_size, min_pages, _ptr(unit_id), _ptr(modality),
-                                      _ptr(pos), _ptr(span), _ptr(cut), _ptr(moved),
-                                      _ptr(workspace), workspace.numel(), _stream(stream)),
-           "omnitide_pack_suffix")
+    ns = n_seg * cap
+    args = (_pool(k, "k"), _dev(v, "v", k.dtype, k.numel()), _kv_dtype(k), n_seg, cap, H, d,
+            page_size, min_pages, _dev(unit_id, "unit_id", _I32, ns),
+            _dev(modality, "modality", _U8, ns), _dev(pos, "pos", _I32, ns),
+            _dev(span, "span", _I32, n_seg), _dev(cut, "cut", _I32, n_seg),
+            _dev(moved, "moved", _I32, n_seg), _buf(workspace), workspace.numel())
+    _check(lib().omnitide_pack_suffix(*args, _stream(stream)), "omnitide_pack_suffix")
 
 
 def omnitide_place_chunk_workspace_bytes(n_seg, cap) -> int:
@@ -583,28 +526,17 @@ def omnitide_place_chunk(k, v, unit_id, modality, pos, k_chunk, v_chunk, chunk_m
     """The chunk into the lowest run of empty slots of pools k/v [n_seg, cap, H, d]."""
     n_seg, cap, H, d = _pool_dims(k, "k")
     L = chunk_modality.numel()
-    _need(k, "k", (torch.bfloat16, torch.float32))
-    _need(v, "v", (k.dtype,), k.numel())
-    _need(unit_id, "unit_id", I32, n_seg * cap)
-    _need(modality, "modality", U8, n_seg * cap)
-    _need(pos, "pos", I32, n_seg * cap)
-    _need(k_chunk, "k_chunk", (k.dtype,), n_seg * L * H * d)
-    _need(v_chunk, "v_chunk", (k.dtype,), n_seg * L * H * d)
-    _need(chunk_modality, "chunk_modality", U8, L)
-    _need(chunk_unit, "chunk_unit", I32, L)
-    for t, nm in ((kept_tokens, "kept_tokens"), (n_kept_units, "n_kept_units"),
-                  (chunk_slot, "chunk_slot"), (span, "span")):
-        _need(t, nm, I32, n_seg)
-    _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_place_chunk(_ptr(k), _ptr(v), _kv_dtype(k), n_seg, cap, H, d,
-                                      _ptr(unit_id), _ptr(modality), _ptr(pos), _ptr(k_chunk),
-                                      _ptr(v_chunk), _ptr(chunk_modality), _ptr(chunk_unit), L,
-                                      _ptr(kept_tokens), _ptr(n_kept_units), _ptr(chunk_slot),
-                                      _ptr(span), _ptr(workspace), workspace.numel(),
-                                      _ptr(d_status), _stream(stream)),
-           "omnitide_place_chunk")
+    ns, nc, dt = n_seg * cap, n_seg * L * H * d, k.dtype
+    args = (_pool(k, "k"), _dev(v, "v", dt, k.numel()), _kv_dtype(k), n_seg, cap, H, d,
+            _dev(unit_id, "unit_id", _I32, ns), _dev(modality, "modality", _U8, ns),
+            _dev(pos, "pos", _I32, ns), _dev(k_chunk, "k_chunk", dt, nc),
+            _dev(v_chunk, "v_chunk", dt, nc), _dev(chunk_modality, "chunk_modality", _U8, L),
+            _dev(chunk_unit, "chunk_unit", _I32, L), L,
+            _dev(kept_tokens, "kept_tokens", _I32, n_seg),
+            _dev(n_kept_units, "n_kept_units", _I32, n_seg),
+            _dev(chunk_slot, "chunk_slot", _I32, n_seg), _dev(span, "span", _I32, n_seg),
+            _buf(workspace), workspace.numel(), _status(d_status))
+    _check(lib().omnitide_place_chunk(*args, _stream(stream)), "omnitide_place_chunk")
 
 
 def omnitide_decode_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads, head_dim) -> int:
@@ -622,17 +554,9 @@ def omnitide_decode_attn(q, k, v, n_ctx, scale, out, workspace=None, d_status=No
     ns, cap, Hkv, dk = _pool_dims(k, "k")
     if ns != n_seg or dk != d:
         raise ValueError("k does not match q")
-    _need(q, "q", (torch.bfloat16,))
-    _need(k, "k", (torch.bfloat16,))
-    _need(v, "v", (torch.bfloat16,), k.numel())
-    _need(n_ctx, "n_ctx", I32, n_seg)
-    _need(out, "out", (torch.float32,), q.numel())
-    if workspace is not None:
-        _need(workspace, "workspace", U8)
-    if d_status is not None:
-        _need(d_status, "d_status", I32, 1)
-    _check(lib().omnitide_decode_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(n_ctx), n_seg, cap, n_q,
-                                      Hq, Hkv, d, float(scale), _ptr(out), _ptr(workspace),
-                                      0 if workspace is None else workspace.numel(),
-                                      _ptr(d_status), _stream(stream)), "omnitide_decode_attn")
-
+    args = (_dev(q, "q", _BF16, q.numel()), _dev(k, "k", _BF16, k.numel()),
+            _dev(v, "v", _BF16, k.numel()), _dev(n_ctx, "n_ctx", _I32, n_seg), n_seg, cap, n_q,
+            Hq, Hkv, d, float(scale), _dev(out, "out", _F32, q.numel()),
+            None if workspace is None else _buf(workspace),
+            0 if workspace is None else workspace.numel(), _status(d_status))
+    _check(lib().omnitide_decode_attn(*args, _stream(stream)), "omnitide_decode_attn")
