@@ -122,7 +122,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   __shared__ float sm[kDecWaves][16], sl[kDecWaves][16];
 
   const int split = blockIdx.x, g = blockIdx.y, seg = blockIdx.z;
+  // all per-segment words in one round trip (before the checks, which the loads could not pass)
   int nctx = n_ctx_g[seg];                          // SPAN, POS: the span
+  const int n_act = SPAN ? n_active_g[seg] : 0;
+  const int qp0 = SPAN || POS ? qpos0_g[seg] : 0;
   if (nctx < nq || nctx > cap) {
     if (threadIdx.x == 0) set_status(status, OMNITIDE_E_CAPACITY);
     return;
@@ -130,7 +133,6 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   if constexpr (POS) {
     // the entries must be exactly the positions 0 .. q_pos0 + n_q - 1 (their number is checked
     // after the loop: every slot taken from the index is clamped, so the loop is safe either way)
-    const int qp0 = qpos0_g[seg];
     if (qp0 < 0 || qp0 > nctx - nq) {
       if (threadIdx.x == 0) set_status(status, OMNITIDE_E_TAGS);
       return;
@@ -140,10 +142,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   const int G = Hq / Hkv;
   const int nqg = nq * G;
   // contiguous: keys [j0, j1); SPAN: steps [j0, j1) of the tile list (two tiles per step)
-  const int n_units_all = SPAN ? (n_active_g[seg] + 1) / 2 : nctx;
+  const int n_units_all = SPAN ? (n_act + 1) / 2 : nctx;
   const int j0 = static_cast<int>(static_cast<long>(n_units_all) * split / n_split);
   const int j1 = static_cast<int>(static_cast<long>(n_units_all) * (split + 1) / n_split);
-  const int n_act = SPAN ? n_active_g[seg] : 0;
   const size_t tl_base = static_cast<size_t>(seg) * max_tiles;
   const int32_t* kpos = SPAN ? key_pos + static_cast<size_t>(seg) * cap : nullptr;
   const int tid = threadIdx.x;
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   const bool col_ok = c16 < nqg;
   const int tok = col_ok ? c16 / G : 0;
   // keys (contiguous: rows; SPAN: positions) <= lim are visible
-  const int lim = SPAN ? qpos0_g[seg] + tok : (col_ok ? nctx - nq + tok : nctx - 1);
+  const int lim = SPAN ? qp0 + tok : (col_ok ? nctx - nq + tok : nctx - 1);
   bf16x8 qf[KC];
   {
     const uint16_t* qrow =
@@ -189,29 +190,29 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   // 64*tile + 16*(wave % 4) with tile the list entry 2*(j0 + it) + wave / 4, rows past the span
   // clamped to its last slot; a wave past the list reads the span's first rows and masks them.
   // Every load is issued unconditionally, so the vmcnt waits below count exactly.
-  auto block_base = [&](int it, bool& blk_ok) {
-    if constexpr (SPAN) {
-      const int a = 2 * (j0 + it) + (wave >> 2);
-      blk_ok = a < n_act;
-      return blk_ok ? kKT * tile_list[tl_base + a] + kKB * (wave & 3) : 0;
-    } else {
-      blk_ok = true;
-      return j0 + it * kStep + kKB * wave;
-    }
+  auto block_base = [&](int it) { return j0 + it * kStep + kKB * wave; };
+  // SPAN: the tile of this wave's next block to issue (-1 past the list), read one block ahead, so
+  // that the block's loads do not wait for the list
+  auto load_tile = [&](int it) {
+    const int a = 2 * (j0 + it) + (wave >> 2);
+    return a < n_act ? tile_list[tl_base + a] : -1;
   };
+  int tile_next = -1;
   const int row_end = SPAN ? nctx : j1;      // rows >= row_end are clamped
   const int n_it = SPAN ? j1 - j0 : (j1 - j0 + kStep - 1) / kStep;
   // POS: slot of this lane's key c16 in the next block to issue (positions past row_end - 1
   // clamped), loaded one iteration ahead
   const int32_t* slot_of = POS ? tile_list + static_cast<size_t>(seg) * cap : nullptr;
   auto load_slot = [&](int it) {
-    bool blk_ok;
-    return slot_of[min(block_base(it, blk_ok) + c16, row_end - 1)];
+    return slot_of[min(block_base(it) + c16, row_end - 1)];
   };
   int slot_next = 0;
-  auto issue = [&](int it, int buf, bf16x8 (&ka)[KC], int (&kp)[5]) {
-    bool blk_ok;
-    const int kb0 = block_base(it, blk_ok);
+  // Issues a block's loads.  base receives its first key (SPAN: the span's end for a block past
+  // the list, so that every key of it is out of range); SPAN: kp the position of key c16.
+  auto issue = [&](int it, int buf, bf16x8 (&ka)[KC], int& kp, int& base) {
+    int kb0 = block_base(it);
+    if constexpr (SPAN) kb0 = tile_next >= 0 ? kKT * tile_next + kKB * (wave & 3) : 0;
+    base = SPAN && tile_next < 0 ? nctx : kb0;
     uint32_t kslot = 0;
     if constexpr (POS) kslot = min(static_cast<uint32_t>(slot_next), static_cast<uint32_t>(cap - 1));
     const int kr = POS ? static_cast<int>(kslot) : min(kb0 + c16, row_end - 1);
@@ -220,10 +221,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     for (int kc = 0; kc < KC; ++kc)
       ka[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kp_ + 32 * kc));
     if constexpr (SPAN) {
-      // positions of keys 4 g4 .. +3 (for the mask) and of key c16 (for the V zeroing)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kp[i] = kpos[min(kb0 + 4 * g4 + i, row_end - 1)];
-      kp[4] = kpos[kr];
+      kp = kpos[kr];
+      tile_next = it + 1 < n_it ? load_tile(it + 1) : -1;
     }
     if constexpr (POS) {
       // V rows of keys vkey[cq] (< 16): their slots are held by lanes vkey[cq]; the host keeps
@@ -253,7 +252,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   for (int db = 0; db < DB; ++db) o[db] = floatx4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   bf16x8 kA[KC], kB[KC];
-  int pA[5] = {-1, -1, -1, -1, -1}, pB[5] = {-1, -1, -1, -1, -1};
+  int pA = -1, pB = -1, bA = 0, bB = 0;    // by block parity: key positions (SPAN), first key
   // V^T operand read: lane (g4, i) takes dims 16db + i of keys 4g4 .. 4g4+3; the lanes of its
   // group read key 4g4 + (i >> 2), dims 16db + 4(i & 3) .. +3.
   const int vrow = 4 * g4 + (c16 >> 2);
@@ -263,23 +262,38 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     constexpr int B = decltype(bpar)::value;
     bf16x8(&ka)[KC] = B == 0 ? kA : kB;
     bf16x8(&kn)[KC] = B == 0 ? kB : kA;
-    const int(&pc)[5] = B == 0 ? pA : pB;
-    int(&pn)[5] = B == 0 ? pB : pA;
+    int& pn = B == 0 ? pB : pA;
+    int& bn = B == 0 ? bB : bA;
+    const int kb0 = B == 0 ? bA : bB;
     const bool more = it + 1 < n_it;
     floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc)
       s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[kc], qf[kc], s, 0, 0, 0);
-    const int(&kpc)[5] = pc;   // positions of this iteration's keys (SPAN)
+    // SPAN: the keys' visibility, decided before the next block's loads go out.  The compiler
+    // counts only the loads it knows when it waits for the position (the V block's direct loads
+    // are assembly), so a wait placed after the next block's loads would wait for some of those
+    // too (the kernel took 18.4 us with the wait there and four more position loads per block, at
+    // 17,361 entries in a span of 37,997 slots).
+    bool hide[4] = {false, false, false, false}, hole = false;
+    if constexpr (SPAN) {
+      const int pc = (B == 0 ? pA : pB);
+      const bool in = kb0 + c16 < nctx;
+      const int kp = in ? pc : -1;           // rows past the span were clamped to its last slot
+      hole = kp < 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int x = __shfl(kp, 4 * g4 + i, kWave);   // key 4 g4 + i: lane c16 = 4 g4 + i
+        hide[i] = x < 0 || x > lim;
+      }
+    }
     // the next iteration's loads go out once this one's K operands are consumed
-    if (more) issue(it + 1, 1 - B, kn, pn);
-    bool blk_ok;
-    const int kb0 = block_base(it, blk_ok);
+    if (more) issue(it + 1, 1 - B, kn, pn, bn);
     const int key0 = kb0 + 4 * g4;
     if constexpr (SPAN) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (!blk_ok || key0 + i >= nctx || kpc[i] < 0 || kpc[i] > lim) s[i] = -INFINITY;
+        if (hide[i]) s[i] = -INFINITY;
     } else if (kb0 + kKB > j1 || kb0 + kKB - 1 > nctx - nq) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -319,14 +333,14 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     // this iteration's V block has landed (the next one's loads may still be in flight: KC K
     // loads, in SPAN mode 5 position loads, CALLS direct loads)
     // (POS: the next block's slot load before them and the one after next's after them)
-    constexpr int NEXT = CALLS + KC + (SPAN ? 5 : 0) + (POS ? 2 : 0);
-    static_assert(NEXT == 8 || NEXT == 4 || NEXT == 13 || NEXT == 9 || NEXT == 10 || NEXT == 6,
+    constexpr int NEXT = CALLS + KC + (SPAN ? 1 : 0) + (POS ? 2 : 0);
+    static_assert(NEXT == 8 || NEXT == 4 || NEXT == 9 || NEXT == 5 || NEXT == 10 || NEXT == 6,
                   "vmcnt immediates below");
     if (more) {
-      if constexpr (NEXT == 13) asm volatile("s_waitcnt vmcnt(13)" ::: "memory");
-      else if constexpr (NEXT == 10) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+      if constexpr (NEXT == 10) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
       else if constexpr (NEXT == 9) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
       else if constexpr (NEXT == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else if constexpr (NEXT == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
       else if constexpr (NEXT == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     } else {
@@ -335,7 +349,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     if constexpr (SPAN) {
       // V rows of empty slots (and of a wave past the list) are zeroed by the four lanes of
       // their key, a quarter of the row each; the wave's own LDS reads below follow in order
-      if (!blk_ok || kpc[4] < 0) {
+      if (hole) {
         u32x4* row = reinterpret_cast<u32x4*>(&vbuf[wave][B][0] + c16 * D);
 #pragma unroll
         for (int x = 0; x < CHK / 4; ++x) row[(CHK / 4) * g4 + x] = u32x4{0, 0, 0, 0};
@@ -353,7 +367,10 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
   if constexpr (POS) {
     if (n_it > 0) slot_next = load_slot(0);
   }
-  if (n_it > 0) issue(0, 0, kA, pA);
+  if constexpr (SPAN) {
+    if (n_it > 0) tile_next = load_tile(0);
+  }
+  if (n_it > 0) issue(0, 0, kA, pA, bA);
   int it = 0;
   for (; it + 1 < n_it; it += 2) {
     step(std::integral_constant<int, 0>{}, it);

@@ -202,3 +202,18 @@ def test_decode_span_capacity_error():
     q = bf16(rng.standard_normal((1, 1, 4, 64)))
     out = run_decode_span(q, k[None], v[None], kp[None], [501], [qp], 0.1, expect_status=-5)
     assert np.isnan(out).all()                     # the segment's output is not written
+
+
+@pytest.mark.parametrize("cap,nq,Hq,Hkv,d,fill,seed", [
+    (130, 1, 8, 1, 128, 0.5, 21),        # three tiles: the second step half past the list
+    (4000, 2, 8, 2, 64, 0.05, 22),       # sparse tiles
+    (70000, 1, 16, 2, 128, 0.02, 23),    # mostly empty tiles, several steps per split
+])
+@pytest.mark.parametrize("skip", [True, False])
+def test_decode_span_blocks_past_the_list(cap, nq, Hq, Hkv, d, fill, seed, skip):
+    """Blocks past the tile list and rows past the span take no part (NaN in every hole)."""
+    rng = np.random.default_rng(seed)
+    k, v, kp, span, qp = random_span_pool(rng, cap, nq, Hkv, d, fill, nan_holes=True)
+    q = bf16(rng.standard_normal((1, nq, Hq, d)))
+    out = run_decode_span(q, k[None], v[None], kp[None], [span], [qp], 0.1, skip=skip)
+    check(out[0], q[0], k, v, kp, span, qp, 0.1)
