@@ -11,8 +11,8 @@
 // every destination tile, the rank of the unit holding the tile's first row.
 // Mask: a count kernel (one wave per unit) gives each unit its kept count, the plan kernel
 // scans those, and a map kernel (one wave per unit, one aligned 16-byte block of the mask per
-// lane, an in-lane count plus one wave scan per 1,024 slots) writes each kept slot's
-// destination row, its tags and its position shift.  Up to 512 units the map kernel builds the
+// lane, an in-lane count plus one wave scan per 1,024 slots) writes each kept slot's unit, source
+// slot and position shift at its destination row.  Up to 512 units the map kernel builds the
 // unit plan in LDS itself (as the copy workgroups do), so no plan kernel runs.
 // Copy: one workgroup per destination tile of kTile rows.  The tile's rows are resolved to
 // source slots (binary search over the LDS table, or a short forward walk from the workspace
@@ -299,7 +299,7 @@ __device__ inline int resolve_rows(int seg, int r0, int span, int nctx, int n_sl
 
   if (tid < nrows) {
     const int r = r0 + tid;
-    if (r < kept && mapped) {                     // the map kernel wrote the row's tags
+    if (r < kept && mapped) {                     // the map kernel wrote unit, source and shift
       const WsLayout L = ws_layout(n_units, cap_dst);
       const int32_t* shift = reinterpret_cast<const int32_t*>(
           ws + static_cast<size_t>(seg) * L.seg_bytes + L.shift_off);
@@ -381,8 +381,9 @@ __device__ inline int resolve_tile(int seg, int t, int nctx, int n_slots, int ch
 }
 
 // The tag writes resolve_rows leaves to its caller when given rank_row: the history rows
-// among destination rows [r0, r0 + nrows) (unless the mask map kernel wrote them) and the chunk
-// rows.  One thread per row.
+// among destination rows [r0, r0 + nrows) (after the mask map kernel only their modality and
+// position, which it leaves to this pass, where they overlap the row copies) and the chunk rows.
+// One thread per row.
 __device__ inline void tile_tags(int seg, int r0, int nrows, int nctx, int n_slots,
                                  int chunk_len, int cap_dst, const uint8_t* __restrict__ mod_src,
                                  const int32_t* __restrict__ pos_src,
@@ -398,12 +399,12 @@ __device__ inline void tile_tags(int seg, int r0, int nrows, int nctx, int n_slo
   const int kept = nctx - chunk_len;
   const size_t d = static_cast<size_t>(seg) * cap_dst + r;
   if (r < kept) {
-    if (mapped) return;
     const int s = src_row[tid];
     const size_t st = static_cast<size_t>(seg) * n_slots + s;
-    uid_dst[d] = rank_row[tid];
     mod_dst[d] = mod_src[st];
     pos_dst[d] = pos_src[st] + shift_row[tid];
+    if (mapped) return;                            // the map kernel wrote the unit and source
+    uid_dst[d] = rank_row[tid];
     src_of_dst[d] = s;
   } else {
     const int i = r - kept;
@@ -963,29 +964,17 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_count_kernel(
 // number `within` of the unit goes to destination row rec_off + within with the unit's new id
 // rk, and its position drops by the deleted live slots before it (rec_del plus those of the
 // unit).  The wave walks aligned 16-slot blocks, 16 per lane per step, with one wave scan of
-// the kept counts per step.  Branch-free per slot: the tag reads and writes of slots that are
-// not kept use an offset past their buffer, which the hardware turns into a zero read and a
-// dropped write.
+// the kept counts per step.  Branch-free per slot: the writes of slots that are not kept use
+// an offset past their buffer, which the hardware drops.
 __device__ inline void map_unit_slots(const uint8_t* m, int f, int n, int rk, int rec_off,
-                                      int rec_del, int lane, int seg, int n_slots, int cap_dst,
-                                      const uint8_t* mod_src, const int32_t* pos_src,
-                                      int32_t* uid_dst, uint8_t* mod_dst, int32_t* pos_dst,
-                                      int32_t* src_of_dst, int32_t* shift) {
+                                      int rec_del, int lane, int seg, int cap_dst,
+                                      int32_t* uid_dst, int32_t* src_of_dst, int32_t* shift) {
   constexpr int P = kUnitPer;
-  const size_t sb = static_cast<size_t>(seg) * n_slots;
   const size_t db = static_cast<size_t>(seg) * cap_dst;
-  const __amdgpu_buffer_rsrc_t r_mod_s =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(mod_src + sb), 0, n_slots, kBufFlags);
-  const __amdgpu_buffer_rsrc_t r_pos_s = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int32_t*>(pos_src + sb), 0, 4 * n_slots, kBufFlags);
   const __amdgpu_buffer_rsrc_t r_src =
       __builtin_amdgcn_make_buffer_rsrc(src_of_dst + db, 0, 4 * cap_dst, kBufFlags);
   const __amdgpu_buffer_rsrc_t r_uid =
       __builtin_amdgcn_make_buffer_rsrc(uid_dst + db, 0, 4 * cap_dst, kBufFlags);
-  const __amdgpu_buffer_rsrc_t r_mod =
-      __builtin_amdgcn_make_buffer_rsrc(mod_dst + db, 0, cap_dst, kBufFlags);
-  const __amdgpu_buffer_rsrc_t r_pos =
-      __builtin_amdgcn_make_buffer_rsrc(pos_dst + db, 0, 4 * cap_dst, kBufFlags);
   const __amdgpu_buffer_rsrc_t r_shift =
       __builtin_amdgcn_make_buffer_rsrc(shift, 0, 4 * cap_dst, kBufFlags);
   const uintptr_t end = reinterpret_cast<uintptr_t>(m + f + n);
@@ -1010,14 +999,9 @@ __device__ inline void map_unit_slots(const uint8_t* m, int f, int n, int rk, in
       const int s = s0 + j;
       const int r = rec_off + within;
       const int delb = rec_del + (s - f) - within;   // deleted live slots before s
-      const int so = keep[j] ? s : kOutOfBuf / 4;    // source slot, or past the buffers
       const int ro = keep[j] ? r : kOutOfBuf / 4;    // destination row, or past the buffers
-      const int mod = __builtin_amdgcn_raw_buffer_load_b8(r_mod_s, so, 0, 0);
-      const int pos = __builtin_amdgcn_raw_buffer_load_b32(r_pos_s, 4 * so, 0, 0);
       __builtin_amdgcn_raw_buffer_store_b32(s, r_src, 4 * ro, 0, 0);
       __builtin_amdgcn_raw_buffer_store_b32(rk, r_uid, 4 * ro, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b8(static_cast<uint8_t>(mod), r_mod, ro, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32(pos - delb, r_pos, 4 * ro, 0, 0);
       __builtin_amdgcn_raw_buffer_store_b32(-delb, r_shift, 4 * ro, 0, 0);
       within += keep[j] ? 1 : 0;
     }
@@ -1027,11 +1011,9 @@ __device__ inline void map_unit_slots(const uint8_t* m, int f, int n, int rk, in
 
 __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_map_kernel(
     const uint8_t* __restrict__ mask_g, const int32_t* __restrict__ len_g,
-    const int32_t* __restrict__ first_g, const uint8_t* __restrict__ mod_src,
-    const int32_t* __restrict__ pos_src, int n_slots, int n_units, int cap_dst,
+    const int32_t* __restrict__ first_g, int n_slots, int n_units, int cap_dst,
     const int32_t* __restrict__ remap_g, const int32_t* __restrict__ n_ctx_g,
-    int32_t* __restrict__ uid_dst, uint8_t* __restrict__ mod_dst, int32_t* __restrict__ pos_dst,
-    int32_t* __restrict__ src_of_dst, uint8_t* __restrict__ ws) {
+    int32_t* __restrict__ uid_dst, int32_t* __restrict__ src_of_dst, uint8_t* __restrict__ ws) {
   const int seg = blockIdx.y;
   const int lane = threadIdx.x & (kWave - 1);
   const int u = blockIdx.x * kUnitWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1046,8 +1028,8 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_map_kernel(
   const RankRec rec = reinterpret_cast<const RankRec*>(wseg + L.rank_off)[rk];
   int32_t* shift = reinterpret_cast<int32_t*>(wseg + L.shift_off);
   const size_t sb = static_cast<size_t>(seg) * n_slots;
-  map_unit_slots(mask_g + sb, f, n, rk, rec.off, rec.del, lane, seg, n_slots, cap_dst, mod_src,
-                 pos_src, uid_dst, mod_dst, pos_dst, src_of_dst, shift);
+  map_unit_slots(mask_g + sb, f, n, rk, rec.off, rec.del, lane, seg, cap_dst, uid_dst, src_of_dst,
+                 shift);
 }
 
 // Up to kSmallUnits units: the plan over the count kernel's per-unit counts is built in LDS by
@@ -1055,10 +1037,9 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_map_kernel(
 // writes unit_remap, n_ctx, n_pages, the kept totals and the capacity status.  Then one wave per
 // unit maps its kept slots as compact_mask_map_kernel does.
 __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_map_fused_kernel(
-    const uint8_t* __restrict__ mask_g, const uint8_t* __restrict__ mod_src,
-    const int32_t* __restrict__ pos_src, int n_slots, int n_units, int chunk_len, int cap_dst,
-    int32_t* __restrict__ uid_dst, uint8_t* __restrict__ mod_dst, int32_t* __restrict__ pos_dst,
-    int32_t* __restrict__ src_of_dst, uint8_t* __restrict__ ws, FusedPlanArgs fp) {
+    const uint8_t* __restrict__ mask_g, int n_slots, int n_units, int chunk_len, int cap_dst,
+    int32_t* __restrict__ uid_dst, int32_t* __restrict__ src_of_dst, uint8_t* __restrict__ ws,
+    FusedPlanArgs fp) {
   __shared__ TilePlan<true> plan;
   const int seg = blockIdx.y;
   const WsLayout L = ws_layout(n_units, cap_dst);
@@ -1081,8 +1062,8 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void compact_mask_map_fused_ker
   const int rec_off = plan.roff[rk], rec_del = plan.rdel[rk];
   int32_t* shift = reinterpret_cast<int32_t*>(wseg + L.shift_off);
   const size_t sb = static_cast<size_t>(seg) * n_slots;
-  map_unit_slots(mask_g + sb, f, n, rk, rec_off, rec_del, lane, seg, n_slots, cap_dst, mod_src,
-                 pos_src, uid_dst, mod_dst, pos_dst, src_of_dst, shift);
+  map_unit_slots(mask_g + sb, f, n, rk, rec_off, rec_del, lane, seg, cap_dst, uid_dst, src_of_dst,
+                 shift);
 }
 
 }  // namespace
@@ -1137,9 +1118,8 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
     if (a.n_units <= kSmallUnits) {
       // the map workgroups plan for themselves
       hipLaunchKernelGGL(compact_mask_map_fused_kernel, ugrid, dim3(kUnitWaves * kWave), 0,
-                         stream, a.keep_slot, a.modality_src, a.pos_src, a.n_slots_src,
-                         a.n_units, a.chunk_len, a.cap_dst, a.unit_id_dst, a.modality_dst,
-                         a.pos_dst, a.src_of_dst, ws, fused_args(a));
+                         stream, a.keep_slot, a.n_slots_src, a.n_units, a.chunk_len, a.cap_dst,
+                         a.unit_id_dst, a.src_of_dst, ws, fused_args(a));
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       return launch_copies<false>(a, stream);
@@ -1151,9 +1131,8 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t stream) {
                        a.cap_dst, a.page_size, a.unit_remap, a.n_ctx, a.n_pages, ws,
                        a.d_status);
     hipLaunchKernelGGL(compact_mask_map_kernel, ugrid, dim3(kUnitWaves * kWave), 0, stream,
-                       a.keep_slot, a.unit_len, a.unit_first, a.modality_src, a.pos_src,
-                       a.n_slots_src, a.n_units, a.cap_dst, a.unit_remap, a.n_ctx,
-                       a.unit_id_dst, a.modality_dst, a.pos_dst, a.src_of_dst, ws);
+                       a.keep_slot, a.unit_len, a.unit_first, a.n_slots_src, a.n_units,
+                       a.cap_dst, a.unit_remap, a.n_ctx, a.unit_id_dst, a.src_of_dst, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_copies<false>(a, stream);

@@ -1,4 +1,5 @@
-// OmniPick span plan in three kernels.
+// OmniPick span plan: a census of the units, the plan, the slot mask.  Up to 512 units the plan is
+// made by every workgroup of the mask kernel (two launches), beyond by a kernel of its own.
 //
 // 1. Census (one wave per unit).  The wave walks its unit's slots 1024 at a time (one aligned
 //    16-byte block of tags per lane) and
@@ -8,7 +9,7 @@
 //    the first sink_video / sink_audio tokens of each video / audio span are sinks (kept while
 //    the unit is retained at all), text tokens get their rank among the unit's text tokens,
 //    everything else is dropped from a partially kept unit.  Per unit: sinks, text tokens.
-// 2. Plan (one workgroup per segment: one wave up to 512 units, 1024 threads beyond).  Each
+// 2. Plan (one wave up to 512 units, a workgroup of 1024 threads per segment beyond).  Each
 //    thread owns up to 8 consecutive units.  Every step of the plan is a scan over units in id
 //    (temporal) order, so the sequential walks of the planner become thresholds on prefix sums:
 //      recent    newest live non-system units whose suffix total (own tokens included) is at
@@ -23,6 +24,8 @@
 //                (tokens and count of earlier candidates) alone.
 // 3. Mark (one thread per slot): the slot stays if its unit is kept whole, or its unit is kept
 //    in part and the slot is a sink or one of the unit's first text_keep text tokens.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -153,33 +156,62 @@ __global__ __launch_bounds__(kCensusWaves * kWave) void span_census_kernel(
   }
 }
 
-template <int T>
-__global__ __launch_bounds__(T) void plan_spans_kernel(
-    const int32_t* __restrict__ len_g, const int32_t* __restrict__ first_g,
-    const int32_t* __restrict__ last_g, const uint32_t* __restrict__ flags_g, int n_slots,
-    int n_units, int low, int high, int recent, int text_budget,
-    int32_t* __restrict__ keep_len_g, int32_t* __restrict__ kept_g, uint8_t* __restrict__ ws,
-    int32_t* __restrict__ status) {
-  __shared__ int32_t scr[T / kWave + 1];
-  const int seg = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int U = n_units;
-  const int per = (U + T - 1) / T;
-  const int u0 = tid * per;
-  const size_t base = static_cast<size_t>(seg) * U;
-  const SpanWs W = span_ws(ws, seg, n_slots, n_units);
+// Scans of the plan over units: by one wave (registers only, no barrier) or by the workgroup.
+template <bool WAVE>
+struct PlanScan {
+  int32_t* scr;                              // workgroup scratch (unused by one wave)
+  __device__ int exclusive_sum(int v, int* total) const {
+    if constexpr (WAVE) {
+      const int inc = wave_inclusive_scan(v);
+      *total = __builtin_amdgcn_readlane(inc, kWave - 1);
+      return inc - v;
+    } else {
+      return block_exclusive_scan(v, scr, total);
+    }
+  }
+  __device__ int sum(int v) const {
+    if constexpr (WAVE) return static_cast<int>(wave_sum_u32(static_cast<uint32_t>(v)));
+    else return block_sum(v, scr);
+  }
+  __device__ int exclusive_max(int v, int lo) const {
+    if constexpr (WAVE) {
+      return wave_exclusive_max_i32(v, lo);
+    } else {
+      int ignored;
+      return block_exclusive_max(v, lo, scr, &ignored);
+    }
+  }
+};
 
-  int ln[kMaxPer], fs[kMaxPer], ls[kMaxPer], sk[kMaxPer], tx[kMaxPer];
+struct SpanPlanIn {
+  const int32_t* len;
+  const int32_t* first;
+  const int32_t* last;
+  const uint32_t* flags;
+  int n_slots, n_units, low, high, recent, text_budget;
+};
+
+// The plan of one segment: thread t owns units [t*per, (t+1)*per).  Leaves the unit lengths (0 past
+// U and for units without slots), kept lengths and kept text tokens of its units in ln, kl and tk,
+// and returns the segment's total, or -1 for malformed units (kl is then 0).
+template <bool WAVE>
+__device__ inline int plan_units(const SpanPlanIn& in, size_t base, const SpanWs& W, int tid,
+                                 int per, const PlanScan<WAVE>& sc, int (&ln)[kMaxPer],
+                                 int (&kl)[kMaxPer], int (&tk)[kMaxPer]) {
+  const int U = in.n_units;
+  const int u0 = tid * per;
+  int fs[kMaxPer], ls[kMaxPer], sk[kMaxPer], tx[kMaxPer];
   uint32_t fl[kMaxPer];
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) {        // all loads first: one memory round trip
     const int u = min(u0 + i, U - 1);
-    ln[i] = len_g[base + u];
-    fs[i] = first_g[base + u];
-    ls[i] = last_g[base + u];
-    fl[i] = flags_g[base + u];
+    ln[i] = in.len[base + u];
+    fs[i] = in.first[base + u];
+    ls[i] = in.last[base + u];
+    fl[i] = in.flags[base + u];
     sk[i] = W.sinks[u];
     tx[i] = W.text[u];
+    kl[i] = tk[i] = 0;
   }
   bool bad = false;
   int my_max_first = -1;
@@ -187,13 +219,12 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
   for (int i = 0; i < kMaxPer; ++i) {
     if (!(i < per && u0 + i < U) || ln[i] <= 0) ln[i] = 0;
     const bool live = ln[i] > 0;
-    const bool in_range = live && fs[i] >= 0 && fs[i] <= n_slots - ln[i];
+    const bool in_range = live && fs[i] >= 0 && fs[i] <= in.n_slots - ln[i];
     bad |= live && (!in_range || ls[i] - fs[i] + 1 != ln[i] || sk[i] < 0);
     if (live) my_max_first = max(my_max_first, fs[i]);
   }
   // live units must appear in unit order
-  int ignored;
-  int run = block_exclusive_max(my_max_first, -1, scr, &ignored);
+  int run = sc.exclusive_max(my_max_first, -1);
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) {
     if (ln[i] > 0) {
@@ -201,32 +232,16 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
       run = max(run, fs[i]);
     }
   }
-  const int n_bad = block_sum(bad ? 1 : 0, scr);
-  auto write_out = [&](const int* kl) {
-#pragma unroll
-    for (int i = 0; i < kMaxPer; ++i)
-      if (i < per && u0 + i < U) keep_len_g[base + u0 + i] = kl[i];
-  };
-  int kl[kMaxPer];
-  if (n_bad > 0) {
-#pragma unroll
-    for (int i = 0; i < kMaxPer; ++i) kl[i] = 0;
-    write_out(kl);
-    if (tid == 0) {
-      kept_g[seg] = 0;
-      set_status(status, OMNITIDE_E_TAGS);
-    }
-    return;
-  }
+  if (sc.sum(bad ? 1 : 0) > 0) return -1;
 
   int my_len = 0;
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) my_len += ln[i];
-  const int total = block_sum(my_len, scr);
-  if (total <= high) {                         // at or below the high watermark: keep all
-    write_out(ln);
-    if (tid == 0) kept_g[seg] = total;
-    return;
+  const int total = sc.sum(my_len);
+  if (total <= in.high) {                      // at or below the high watermark: keep all
+#pragma unroll
+    for (int i = 0; i < kMaxPer; ++i) kl[i] = ln[i];
+    return total;
   }
 
   bool sys[kMaxPer];
@@ -238,7 +253,7 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
   }
   // recent window: suffix sums of eligible lengths
   int elig_total;
-  const int elig_before = block_exclusive_scan(my_elig, scr, &elig_total);
+  const int elig_before = sc.exclusive_sum(my_elig, &elig_total);
   int suffix = elig_total - elig_before - my_elig;
   bool rec[kMaxPer];
 #pragma unroll
@@ -246,7 +261,7 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
     rec[i] = false;
     if (ln[i] > 0 && !sys[i]) {
       suffix += ln[i];
-      rec[i] = suffix <= recent;
+      rec[i] = suffix <= in.recent;
     }
   }
   // older units: their sinks, and text tokens under the shared budget (oldest first)
@@ -254,21 +269,20 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) my_text += (ln[i] > 0 && !sys[i] && !rec[i]) ? tx[i] : 0;
   int text_total;
-  int text_before = block_exclusive_scan(my_text, scr, &text_total);
+  int text_before = sc.exclusive_sum(my_text, &text_total);
   int my_kept = 0, my_part = 0, my_part_n = 0, my_comp = 0, my_comp_n = 0, my_ret = 0;
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) {
-    int k = 0, tk = 0;
+    int k = 0;
     if (ln[i] > 0) {
       if (sys[i] || rec[i]) {
         k = ln[i];
       } else {
-        tk = min(tx[i], max(text_budget - text_before, 0));
-        k = sk[i] + tk;
+        tk[i] = min(tx[i], max(in.text_budget - text_before, 0));
+        k = sk[i] + tk[i];
         text_before += tx[i];
       }
     }
-    if (i < per && u0 + i < U) W.text_keep[u0 + i] = tk;
     kl[i] = k;
     my_kept += k;
     my_ret += k > 0 ? 1 : 0;
@@ -280,13 +294,13 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
       ++my_comp_n;
     }
   }
-  const int kept0 = block_sum(my_kept, scr);
-  const int retained0 = block_sum(my_ret, scr);
+  const int kept0 = sc.sum(my_kept);
+  const int retained0 = sc.sum(my_ret);
   int part_tok, part_n, comp_tok, comp_n;
-  int part_before = block_exclusive_scan(my_part, scr, &part_tok);
-  int part_rank = block_exclusive_scan(my_part_n, scr, &part_n);
-  int comp_before = block_exclusive_scan(my_comp, scr, &comp_tok);
-  int comp_rank = block_exclusive_scan(my_comp_n, scr, &comp_n);
+  int part_before = sc.exclusive_sum(my_part, &part_tok);
+  int part_rank = sc.exclusive_sum(my_part_n, &part_n);
+  int comp_before = sc.exclusive_sum(my_comp, &comp_tok);
+  int comp_rank = sc.exclusive_sum(my_comp_n, &comp_n);
   (void)comp_tok;
   (void)comp_n;
   int my_final = 0;
@@ -295,22 +309,51 @@ __global__ __launch_bounds__(T) void plan_spans_kernel(
     const int k = kl[i];
     if (k > 0 && k < ln[i]) {
       // candidate number part_rank (0-based) of the drop order
-      if (kept0 - part_before > low && retained0 - part_rank > 1) kl[i] = 0;
+      if (kept0 - part_before > in.low && retained0 - part_rank > 1) kl[i] = 0;
       part_before += k;
       ++part_rank;
     } else if (k > 0 && !sys[i]) {
-      if (kept0 - part_tok - comp_before > low && retained0 - part_n - comp_rank > 1) kl[i] = 0;
+      if (kept0 - part_tok - comp_before > in.low && retained0 - part_n - comp_rank > 1) kl[i] = 0;
       comp_before += k;
       ++comp_rank;
     }
     my_final += kl[i];
   }
-  write_out(kl);
-  const int kept = block_sum(my_final, scr);
-  if (tid == 0) kept_g[seg] = kept;
+  return sc.sum(my_final);
 }
 
-}  // namespace
+// Plan of more than kMarkUnits units, one workgroup per segment.
+constexpr int kPlanThreads = 1024;
+
+__global__ __launch_bounds__(kPlanThreads) void plan_spans_kernel(
+    SpanPlanIn in, int32_t* __restrict__ keep_len_g, int32_t* __restrict__ kept_g,
+    uint8_t* __restrict__ ws, int32_t* __restrict__ status) {
+  __shared__ int32_t scr[kPlanThreads / kWave + 1];
+  const int seg = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int per = (in.n_units + kPlanThreads - 1) / kPlanThreads;
+  const size_t base = static_cast<size_t>(seg) * in.n_units;
+  const SpanWs W = span_ws(ws, seg, in.n_slots, in.n_units);
+  int ln[kMaxPer], kl[kMaxPer], tk[kMaxPer];
+  const int kept = plan_units<false>(in, base, W, tid, per, PlanScan<false>{scr}, ln, kl, tk);
+#pragma unroll
+  for (int i = 0; i < kMaxPer; ++i) {
+    const int u = tid * per + i;
+    if (i < per && u < in.n_units) {
+      keep_len_g[base + u] = kl[i];
+      W.text_keep[u] = tk[i];
+    }
+  }
+  if (tid == 0) {
+    kept_g[seg] = max(kept, 0);
+    if (kept < 0) set_status(status, OMNITIDE_E_TAGS);
+  }
+}
+
+// The slot's keep flag, given its unit's length, kept length and kept text tokens.
+__device__ inline uint8_t slot_kept(int ln, int kl, int tk, int32_t code) {
+  return kl > 0 && (kl >= ln || code == kInfoSink || (code >= 0 && code < tk)) ? 1 : 0;
+}
 
 constexpr int kMarkThreads = 256;
 
@@ -328,17 +371,69 @@ __global__ __launch_bounds__(kMarkThreads) void span_mark_kernel(
   if (u >= 0 && u < n_units) {
     const int kl = keep_len_g[ub + u];
     if (kl > 0) {
-      if (kl >= len_g[ub + u]) {
-        out = 1;
-      } else {
-        const SpanWs W = span_ws(ws, seg, n_slots, n_units);
-        const int32_t code = W.info[s];
-        out = (code == kInfoSink || (code >= 0 && code < W.text_keep[u])) ? 1 : 0;
-      }
+      const SpanWs W = span_ws(ws, seg, n_slots, n_units);
+      out = slot_kept(len_g[ub + u], kl, W.text_keep[u], W.info[s]);
     }
   }
   keep_slot_g[sb + s] = out;
 }
+
+// Plan and mask in one launch for up to kMarkUnits units: wave 0 of every workgroup plans the
+// segment into LDS (about 2 us, in all workgroups at once) while the other waves' tags and codes
+// are on their way, then the workgroup marks its kMarkSlots slots; workgroup 0 writes the plan
+// out.  Latency-bound: as two launches the plan took 5.4 us and the mask 3.3 us at 358 units
+// and 81,920 slots.
+constexpr int kMarkUnits = kWave * kMaxPer;
+constexpr int kMarkPer = 4;
+constexpr int kMarkSlots = kMarkThreads * kMarkPer;
+
+__global__ __launch_bounds__(kMarkThreads) void span_plan_mark_kernel(
+    SpanPlanIn in, const int32_t* __restrict__ uid_g, int32_t* __restrict__ keep_len_g,
+    int32_t* __restrict__ kept_g, uint8_t* __restrict__ ws, uint8_t* __restrict__ keep_slot_g,
+    int32_t* __restrict__ status) {
+  __shared__ int32_t s_len[kMarkUnits], s_keep[kMarkUnits], s_text[kMarkUnits];
+  const int seg = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int U = in.n_units;
+  const size_t base = static_cast<size_t>(seg) * U;
+  const size_t sb = static_cast<size_t>(seg) * in.n_slots;
+  const SpanWs W = span_ws(ws, seg, in.n_slots, U);
+  int uid[kMarkPer], code[kMarkPer];
+#pragma unroll
+  for (int i = 0; i < kMarkPer; ++i) {
+    const int s = blockIdx.x * kMarkSlots + i * kMarkThreads + tid;
+    uid[i] = s < in.n_slots ? uid_g[sb + s] : -1;
+    code[i] = s < in.n_slots ? W.info[s] : 0;      // garbage for slots of no unit, unused
+  }
+  if (tid < kWave) {
+    int ln[kMaxPer], kl[kMaxPer], tk[kMaxPer];
+    const int kept = plan_units<true>(in, base, W, tid, kMaxPer, PlanScan<true>{nullptr}, ln, kl,
+                                      tk);
+#pragma unroll
+    for (int i = 0; i < kMaxPer; ++i) {
+      const int u = kMaxPer * tid + i;
+      s_len[u] = ln[i];
+      s_keep[u] = kl[i];
+      s_text[u] = tk[i];
+      if (blockIdx.x == 0 && u < U) keep_len_g[base + u] = kl[i];
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+      kept_g[seg] = max(kept, 0);
+      if (kept < 0) set_status(status, OMNITIDE_E_TAGS);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kMarkPer; ++i) {
+    const int s = blockIdx.x * kMarkSlots + i * kMarkThreads + tid;
+    if (s >= in.n_slots) continue;
+    const int u = uid[i];
+    keep_slot_g[sb + s] =
+        u >= 0 && u < U ? slot_kept(s_len[u], s_keep[u], s_text[u], code[i]) : 0;
+  }
+}
+
+}  // namespace
 
 hipError_t launch_plan_spans(const SpanPlanArgs& a, hipStream_t stream) {
   uint8_t* ws = static_cast<uint8_t*>(a.workspace);
@@ -346,16 +441,17 @@ hipError_t launch_plan_spans(const SpanPlanArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(span_census_kernel, cgrid, dim3(kCensusWaves * kWave), 0, stream,
                      a.modality, a.unit_len, a.unit_first, a.n_slots, a.n_units, a.sink_video,
                      a.sink_audio, ws, a.d_status);
-  if (a.n_units <= 64 * kMaxPer)
-    hipLaunchKernelGGL(plan_spans_kernel<64>, dim3(a.n_seg), dim3(64), 0, stream, a.unit_len,
-                       a.unit_first, a.unit_last, a.unit_flags, a.n_slots, a.n_units, a.low,
-                       a.high, a.recent, a.text_budget, a.keep_len, a.kept_tokens, ws,
-                       a.d_status);
-  else
-    hipLaunchKernelGGL(plan_spans_kernel<1024>, dim3(a.n_seg), dim3(1024), 0, stream, a.unit_len,
-                       a.unit_first, a.unit_last, a.unit_flags, a.n_slots, a.n_units, a.low,
-                       a.high, a.recent, a.text_budget, a.keep_len, a.kept_tokens, ws,
-                       a.d_status);
+  const SpanPlanIn in{a.unit_len, a.unit_first, a.unit_last, a.unit_flags, a.n_slots,
+                      a.n_units,  a.low,        a.high,      a.recent,     a.text_budget};
+  if (a.n_units <= kMarkUnits) {
+    // one workgroup at least: it writes the plan also for a pool without slots
+    const dim3 grid(std::max(1, (a.n_slots + kMarkSlots - 1) / kMarkSlots), a.n_seg);
+    hipLaunchKernelGGL(span_plan_mark_kernel, grid, dim3(kMarkThreads), 0, stream, in, a.unit_id,
+                       a.keep_len, a.kept_tokens, ws, a.keep_slot, a.d_status);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(plan_spans_kernel, dim3(a.n_seg), dim3(kPlanThreads), 0, stream, in,
+                     a.keep_len, a.kept_tokens, ws, a.d_status);
   if (a.n_slots > 0) {
     const dim3 mgrid((a.n_slots + kMarkThreads - 1) / kMarkThreads, a.n_seg);
     hipLaunchKernelGGL(span_mark_kernel, mgrid, dim3(kMarkThreads), 0, stream, a.unit_id,
