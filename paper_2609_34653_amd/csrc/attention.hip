@@ -178,22 +178,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_kernel(
   __shared__ int32_t kpos_lds[SPAN ? kKT : 1];     // positions of the current tile's keys
   __shared__ __attribute__((aligned(16))) int32_t slot_ring[POS ? 4 * kKT : 1];  // tiles t..t+3
 
+  // The per-segment words are on their way while the workgroup finds its place and asks for its
+  // query rows, which depend on none of them; the checks come after (ahead of any K or V access).
   const int seg = blockIdx.y;
   int nctx = n_ctx_g[seg];                         // SPAN, POS: the span
-  if (nctx < L || nctx > cap) {
-    if (threadIdx.x == 0) set_status(status, OMNITIDE_E_CAPACITY);
-    return;
-  }
-  if constexpr (POS) {
-    // the entries must be exactly the positions 0 .. q_pos0 + L - 1 (their number is checked
-    // after the loop: the index clamps every slot it hands out, so the loop is safe either way)
-    const int qp0 = qpos0_g[seg];
-    if (qp0 < 0 || qp0 > nctx - L) {
-      if (threadIdx.x == 0) set_status(status, OMNITIDE_E_TAGS);
-      return;
-    }
-    nctx = qp0 + L;
-  }
+  const int qp0 = SPAN || POS ? qpos0_g[seg] : 0;
+  const int n_listed = SPAN ? list_n[seg] : 0;
   // XCD-aware order: blocks b with equal b % 8 run on one XCD; give them consecutive work ids.
   const int nb = gridDim.x, b = blockIdx.x;
   const int xcd = b % kNumXcd, q8 = nb / kNumXcd, r8 = nb % kNumXcd;
@@ -204,15 +194,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_kernel(
 
   const int G = Hq / Hkv;
   const int rows = L * G;
-  const int kept = SPAN ? qpos0_g[seg] : nctx - L;  // logical position of chunk query 0
   const int m0 = mt * kRowsWG;
   const int p_lo = m0 / G;
   const int p_hi = min(L - 1, (m0 + kRowsWG - 1) / G);
-  const int kmax = kept + p_hi + 1;               // keys [0, kmax) are needed by this workgroup
-  const int n_tiles = SPAN ? list_n[seg] : (kmax + kKT - 1) / kKT;
-  const int t_begin = static_cast<int>(static_cast<long>(n_tiles) * split / n_split);
-  const int t_end = static_cast<int>(static_cast<long>(n_tiles) * (split + 1) / n_split);
-  const int full_lim = kept + p_lo;               // keys <= full_lim are visible to every row
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -223,7 +207,6 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_kernel(
   const bool row_ok = m < rows;
   const int p = row_ok ? m / G : L - 1;
   const int head = g * G + (row_ok ? m % G : 0);
-  const int lim = kept + p;
 
   // Q^T operand: lane holds q[p][head][16c + 8h .. +8] for every 16-wide chunk c of d.
   bf16x8 qf[D / 16];
@@ -235,6 +218,27 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_kernel(
       qf[c] = __builtin_bit_cast(bf16x8, t);
     }
   }
+
+  if (nctx < L || nctx > cap) {
+    if (threadIdx.x == 0) set_status(status, OMNITIDE_E_CAPACITY);
+    return;
+  }
+  if constexpr (POS) {
+    // the entries must be exactly the positions 0 .. q_pos0 + L - 1 (their number is checked
+    // after the loop: the index clamps every slot it hands out, so the loop is safe either way)
+    if (qp0 < 0 || qp0 > nctx - L) {
+      if (threadIdx.x == 0) set_status(status, OMNITIDE_E_TAGS);
+      return;
+    }
+    nctx = qp0 + L;
+  }
+  const int kept = SPAN ? qp0 : nctx - L;         // logical position of chunk query 0
+  const int kmax = kept + p_hi + 1;               // keys [0, kmax) are needed by this workgroup
+  const int n_tiles = SPAN ? n_listed : (kmax + kKT - 1) / kKT;
+  const int t_begin = static_cast<int>(static_cast<long>(n_tiles) * split / n_split);
+  const int t_end = static_cast<int>(static_cast<long>(n_tiles) * (split + 1) / n_split);
+  const int full_lim = kept + p_lo;               // keys <= full_lim are visible to every row
+  const int lim = kept + p;
 
   const size_t kv_seg = static_cast<size_t>(seg) * cap;
   const int row_stride = Hkv * D;
