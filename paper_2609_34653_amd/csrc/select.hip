@@ -54,10 +54,20 @@ constexpr int kCountShift = 44;
 static_assert(kSelWaves == 16, "wave totals are read by lanes 0..15");
 static_assert(kMaxUnits < (1 << (64 - kCountShift)), "a bucket's count field");
 
+// Bitwise OR over the wave, the same in every lane (the DPP steps of the wave scans).
+__device__ inline uint32_t wave_or_u32(uint32_t v) {
+  int x = static_cast<int>(v);
+  x |= dpp_move<kDppRowShr1, 0xf>(0, x);
+  x |= dpp_move<kDppRowShr2, 0xf>(0, x);
+  x |= dpp_move<kDppRowShr4, 0xf>(0, x);
+  x |= dpp_move<kDppRowShr8, 0xf>(0, x);
+  x |= dpp_move<kDppRowBcast15, 0xa>(0, x);
+  x |= dpp_move<kDppRowBcast31, 0xc>(0, x);
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(x, kWave - 1));
+}
 __device__ inline uint64_t wave_or_u64(uint64_t v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off, kWave);
-  return v;
+  return (static_cast<uint64_t>(wave_or_u32(static_cast<uint32_t>(v >> 32))) << 32) |
+         wave_or_u32(static_cast<uint32_t>(v));
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
