@@ -18,7 +18,6 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kMaxUnits = OMNITIDE_MAX_UNITS;
-constexpr int kPer = kMaxUnits / kSelThreads;
 constexpr int kIdBits = 13;   // 2^13 = kMaxUnits
 // Scores below 2^51 fit the 64-bit ranking key (score << kIdBits | id) with one bit to spare.
 // omnitide_score_units never exceeds 2^43: a slot contributes at most 4,096 elements x 2^21 x
@@ -43,9 +42,10 @@ __device__ inline uint64_t udiv64(uint64_t n, uint32_t d) {
 // start at the highest bit in which two candidates differ, so the first pass already spreads
 // the candidates over most buckets and two or three passes end the search.  A bucket holds its
 // candidates' token total (low 44 bits) and their number (high 20) in one 64-bit LDS atomic.
-// Bound by latency: barriers and LDS round trips of one workgroup.  A full bitonic sort of the
-// keys in LDS (78 barrier-separated steps at 4,096) took 74.5 us at 3,880 units; this takes
-// about 15 us (score and selection together 117.5 -> 57.7 us).
+// Bound by latency (barriers and LDS round trips) and by the one CU's instruction issue, so the
+// units per thread are a template argument (1, 2, 4 or 8).  A full bitonic sort of the keys in LDS
+// (78 barrier-separated steps at 4,096) took 74.5 us at 3,880 units; this takes 11.8 us, 13.5 with
+// eight units' code for every thread.
 constexpr int kWideDigitBits = 12;
 constexpr int kWideBuckets = 1 << kWideDigitBits;
 constexpr int kWidePer = kWideBuckets / kSelThreads;
@@ -70,6 +70,7 @@ __device__ inline uint64_t wave_or_u64(uint64_t v) {
          wave_or_u32(static_cast<uint32_t>(v));
 }
 
+template <int PER>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const uint64_t* __restrict__ wsum_g, const int32_t* __restrict__ len_g,
     const int32_t* __restrict__ first_g, const int32_t* __restrict__ last_g,
@@ -91,11 +92,11 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   const int u0 = tid * per;
   const size_t base = static_cast<size_t>(seg) * U;
 
-  int ln[kPer], fs[kPer], ls[kPer];
-  uint32_t fl[kPer];
-  uint64_t ws[kPer];
+  int ln[PER], fs[PER], ls[PER];
+  uint32_t fl[PER];
+  uint64_t ws[PER];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {           // all loads first: one memory round trip
+  for (int i = 0; i < PER; ++i) {           // all loads first: one memory round trip
     ln[i] = fs[i] = ls[i] = 0;
     fl[i] = 0;
     ws[i] = 0;
@@ -110,12 +111,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   }
 #pragma unroll
   for (int j = 0; j < kWidePer; ++j) hist[kWidePer * tid + j] = 0;
-  bool sys[kPer];
-  uint64_t key[kPer];
+  bool sys[PER];
+  uint64_t key[PER];
   bool bad = false, big = false;
   int my_max_first = -1, my_sys = 0, my_elig = 0;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     const bool mine = i < per && u < U;
     if (!mine || ln[i] <= 0) ln[i] = 0;
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   int run = max(max_before, dpp_move<kDppWaveShr1, 0xf>(-1, inc_max));
   bad = false;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     if (ln[i] > 0) {
       bad |= fs[i] <= run;
       run = max(run, fs[i]);
@@ -168,10 +169,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   // recent window: suffix sums of eligible (live, non-system) lengths
   const int cap_rec = min(recent, budget - t_sys);
   int suffix = elig_total - elig_before_wave - inc_elig;   // eligible tokens in later threads
-  bool rec[kPer];
+  bool rec[PER];
   int my_rec = 0;
 #pragma unroll
-  for (int i = kPer - 1; i >= 0; --i) {
+  for (int i = PER - 1; i >= 0; --i) {
     rec[i] = false;
     if (ln[i] > 0 && !sys[i]) {
       suffix += ln[i];
@@ -180,10 +181,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     }
   }
   // candidates (state: 1 active, 2 kept, 0 dropped), and the bits in which their keys differ
-  int state[kPer];
+  int state[PER];
   uint64_t k_or = 0, k_zero = 0;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     state[i] = (ln[i] > 0 && !sys[i] && !rec[i]) ? 1 : 0;
     k_or |= state[i] ? key[i] : 0;
     k_zero |= state[i] ? ~key[i] : 0;
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const int lo = max(hi - kWideDigitBits, 0);
     const uint64_t mask = (1ull << (hi - lo)) - 1;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
+    for (int i = 0; i < PER; ++i)
       if (state[i] == 1)
         atomicAdd(&hist[(key[i] >> lo) & mask],
                   (1ull << kCountShift) + static_cast<uint32_t>(ln[i]));
@@ -268,14 +269,14 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     if (cut < 0) {                                  // every active candidate fits
       taken = s_all;
 #pragma unroll
-      for (int i = 0; i < kPer; ++i)
+      for (int i = 0; i < PER; ++i)
         if (state[i] == 1) state[i] = 2;
       break;
     }
     taken = s_taken;
     const bool last = s_left <= 1 || lo == 0;       // one key left in the bucket: the misfit
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
       if (state[i] == 1) {
         const int dg = static_cast<int>((key[i] >> lo) & mask);
         state[i] = dg > cut ? 2 : (dg < cut || last) ? 0 : 1;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     hi = lo;
   }
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     if (i < per && u < U) keep_g[base + u] = (sys[i] || rec[i] || state[i] == 2) ? 1 : 0;
   }
@@ -513,10 +514,18 @@ hipError_t launch_select(const uint64_t* wsum, const int32_t* len, const int32_t
     hipLaunchKernelGGL(select_small_kernel, dim3(n_seg), dim3(kWave), 0, stream, wsum, len,
                        first, last, flags, n_units, budget, recent, score, keep, kept_tokens,
                        status);
+#define OMNITIDE_SELECT_CASE(PER)                                                               \
+  else if (n_units <= PER * kSelThreads)                                                        \
+    hipLaunchKernelGGL(select_kernel<PER>, dim3(n_seg), dim3(kSelThreads), 0, stream, wsum,     \
+                       len, first, last, flags, n_units, budget, recent, score, keep,           \
+                       kept_tokens, status);
+  OMNITIDE_SELECT_CASE(1)
+  OMNITIDE_SELECT_CASE(2)
+  OMNITIDE_SELECT_CASE(4)
+  OMNITIDE_SELECT_CASE(8)
+#undef OMNITIDE_SELECT_CASE
   else
-    hipLaunchKernelGGL(select_kernel, dim3(n_seg), dim3(kSelThreads), 0, stream, wsum, len,
-                       first, last, flags, n_units, budget, recent, score, keep, kept_tokens,
-                       status);
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
