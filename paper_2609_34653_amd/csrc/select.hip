@@ -1,4 +1,4 @@
-// Budgeted whole-unit selection, one workgroup per segment.  Up to 512 units: a single wave
+// Budgeted whole-unit selection, one workgroup per segment.  Up to 128 units: a single wave
 // (select_small_kernel); beyond: 1024 threads (select_kernel).
 //
 // Groups (paper: must-keep, recent-context, selected-history):
@@ -36,7 +36,7 @@ __device__ inline uint64_t udiv64(uint64_t n, uint32_t d) {
   return n / d;
 }
 
-// Beyond 512 units: the budget cut by the same radix select as the single-wave variant below,
+// Beyond 128 units: the budget cut by the same radix select as the single-wave variant below,
 // over a workgroup.  Thread t owns units [t*per, (t+1)*per); its keys stay in registers.  Digits
 // are 12 bits (4,096 buckets; thread t scans buckets 4095 - 4t .. 4092 - 4t, highest first) and
 // start at the highest bit in which two candidates differ, so the first pass already spreads
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   if (tid == 0) kept_tokens_g[seg] = t_sys + t_rec + taken;
 }
 
-// Single-wave variant for U <= 512 (every lane owns 8 consecutive units): the same plan with
+// Single-wave variant for U <= 128 (every lane owns PER consecutive units): the same plan with
 // wave-level scans (no workgroup barriers) and, instead of a full sort, an MSD radix select of
 // the cut.  The walk "rank order, stop at the first misfit" keeps exactly the candidates whose
 // key exceeds the first misfit's key; the misfit is found digit by digit: a histogram of
@@ -301,8 +301,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
 // locate the bucket where the running total first exceeds the cap; higher buckets are kept,
 // lower ones dropped, and the search continues inside that bucket until it holds one key.
 // Digits are 10 bits wide (1,024 buckets), so a 50-bit key takes five passes.
-constexpr int kSmallUnits = 512;
-constexpr int kSmallPer = kSmallUnits / kWave;
 constexpr int kDigitBits = 10;                       // radix-select digit
 constexpr int kBuckets = 1 << kDigitBits;
 constexpr int kBucketsPerLane = kBuckets / kWave;
@@ -314,6 +312,7 @@ __device__ inline int wave_exclusive_sum(int v, int* total) {
   return inc - v;
 }
 
+template <int PER>
 __global__ __launch_bounds__(kWave) void select_small_kernel(
     const uint64_t* __restrict__ wsum_g, const int32_t* __restrict__ len_g,
     const int32_t* __restrict__ first_g, const int32_t* __restrict__ last_g,
@@ -324,14 +323,14 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   const int seg = blockIdx.x;
   const int lane = threadIdx.x;
   const int U = n_units;
-  const int u0 = lane * kSmallPer;
+  const int u0 = lane * PER;
   const size_t base = static_cast<size_t>(seg) * U;
 
-  int ln[kSmallPer], fs[kSmallPer], ls[kSmallPer];
-  uint32_t fl[kSmallPer];
-  uint64_t ws[kSmallPer];
+  int ln[PER], fs[PER], ls[PER];
+  uint32_t fl[PER];
+  uint64_t ws[PER];
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {      // all loads first: one memory round trip
+  for (int i = 0; i < PER; ++i) {      // all loads first: one memory round trip
     const int u = min(u0 + i, U - 1);
     ln[i] = len_g[base + u];
     fs[i] = first_g[base + u];
@@ -339,12 +338,12 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
     fl[i] = flags_g[base + u];
     ws[i] = wsum_g[base + u];
   }
-  bool sys[kSmallPer];
-  uint64_t key[kSmallPer];
+  bool sys[PER];
+  uint64_t key[PER];
   bool bad = false, big = false;
   int my_max_first = -1;
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     if (u >= U || ln[i] <= 0) ln[i] = 0;
     const bool live = ln[i] > 0;
@@ -359,7 +358,7 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   // unit order: every live unit's first slot exceeds all earlier live units' first slots
   int run = wave_exclusive_max_i32(my_max_first, -1);
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     if (ln[i] > 0) {
       bad |= fs[i] <= run;
       run = max(run, fs[i]);
@@ -367,7 +366,7 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   }
   int my_sys = 0, my_elig = 0;
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     my_sys += sys[i] ? ln[i] : 0;
     my_elig += (ln[i] > 0 && !sys[i]) ? ln[i] : 0;
   }
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   const bool any_big = __any(big);
   if (any_bad || any_big || t_sys > budget) {
 #pragma unroll
-    for (int i = 0; i < kSmallPer; ++i)
+    for (int i = 0; i < PER; ++i)
       if (u0 + i < U) keep_g[base + u0 + i] = 0;
     if (lane == 0) {
       kept_tokens_g[seg] = 0;
@@ -391,10 +390,10 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   // recent window: suffix sums of eligible lengths, newest unit first
   const int cap_rec = min(recent, budget - t_sys);
   int suffix = elig_total - elig_before - my_elig;
-  bool rec[kSmallPer];
+  bool rec[PER];
   int my_rec = 0;
 #pragma unroll
-  for (int i = kSmallPer - 1; i >= 0; --i) {
+  for (int i = PER - 1; i >= 0; --i) {
     rec[i] = false;
     if (ln[i] > 0 && !sys[i]) {
       suffix += ln[i];
@@ -407,10 +406,10 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
   const int cap_sel = budget - t_sys - t_rec;
 
   // radix select of the first misfit among candidates (state: 1 active, 2 kept, 0 dropped)
-  int state[kSmallPer];
+  int state[PER];
   uint64_t kmax = 0;
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     state[i] = (ln[i] > 0 && !sys[i] && !rec[i]) ? 1 : 0;
     if (state[i]) kmax = max(kmax, key[i]);
   }
@@ -426,7 +425,7 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
       *reinterpret_cast<int4*>(&hist[kBucketsPerLane * lane + 4 * j]) = make_int4(0, 0, 0, 0);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kSmallPer; ++i)
+    for (int i = 0; i < PER; ++i)
       if (state[i] == 1) atomicAdd(&hist[(key[i] >> lo) & mask], ln[i]);
     __syncthreads();
     // descending digit order: lane owns digits kBuckets-1 - kBucketsPerLane*lane - j
@@ -456,14 +455,14 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
     const uint64_t cut_lanes = __ballot(cut >= 0);
     if (cut_lanes == 0) {                          // every active candidate fits
 #pragma unroll
-      for (int i = 0; i < kSmallPer; ++i)
+      for (int i = 0; i < PER; ++i)
         if (state[i] == 1) state[i] = 2;
       break;
     }
     const int d_cut = __shfl(cut, __builtin_ctzll(cut_lanes), kWave);
     int my_above = 0;
 #pragma unroll
-    for (int i = 0; i < kSmallPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
       if (state[i] == 1) {
         const int dg = static_cast<int>((key[i] >> lo) & mask);
         if (dg > d_cut) {
@@ -476,7 +475,7 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
     }
     int above, my_left = 0, left;
 #pragma unroll
-    for (int i = 0; i < kSmallPer; ++i) my_left += state[i] == 1 ? 1 : 0;
+    for (int i = 0; i < PER; ++i) my_left += state[i] == 1 ? 1 : 0;
     wave_exclusive_sum(my_above, &above);
     wave_exclusive_sum(my_left, &left);
     taken += above;
@@ -484,14 +483,14 @@ __global__ __launch_bounds__(kWave) void select_small_kernel(
     __syncthreads();
     if (hi == 0 || left <= 1) {                    // one key left in the bucket: the misfit
 #pragma unroll
-      for (int i = 0; i < kSmallPer; ++i)
+      for (int i = 0; i < PER; ++i)
         if (state[i] == 1) state[i] = 0;
       break;
     }
   }
   int my_sel = 0;
 #pragma unroll
-  for (int i = 0; i < kSmallPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     if (u < U) {
       const bool kp = sys[i] || rec[i] || state[i] == 2;
@@ -510,21 +509,30 @@ hipError_t launch_select(const uint64_t* wsum, const int32_t* len, const int32_t
                          const int32_t* last, const uint32_t* flags, int n_seg, int n_units,
                          int budget, int recent, uint64_t* score, uint8_t* keep,
                          int32_t* kept_tokens, int32_t* status, hipStream_t stream) {
-  if (n_units <= kSmallUnits)
-    hipLaunchKernelGGL(select_small_kernel, dim3(n_seg), dim3(kWave), 0, stream, wsum, len,
-                       first, last, flags, n_units, budget, recent, score, keep, kept_tokens,
-                       status);
+  // One wave up to 128 units, a workgroup beyond: the plan of a wave is bound by its instructions,
+  // which grow with the units per lane (by graph replay: 37 units 3.1 us with one per lane, 6.7 with
+  // eight; 128 units 3.3 with two; 256 units 5.2 with four, 474 units 8.3 with eight, where the
+  // workgroup takes 4.6).
+#define OMNITIDE_SELECT_SMALL(PER)                                                              \
+  if (n_units <= PER * kWave)                                                                   \
+    hipLaunchKernelGGL(select_small_kernel<PER>, dim3(n_seg), dim3(kWave), 0, stream, wsum,     \
+                       len, first, last, flags, n_units, budget, recent, score, keep,           \
+                       kept_tokens, status);                                                    \
+  else
+  OMNITIDE_SELECT_SMALL(1)
+  OMNITIDE_SELECT_SMALL(2)
+#undef OMNITIDE_SELECT_SMALL
 #define OMNITIDE_SELECT_CASE(PER)                                                               \
-  else if (n_units <= PER * kSelThreads)                                                        \
+  if (n_units <= PER * kSelThreads)                                                             \
     hipLaunchKernelGGL(select_kernel<PER>, dim3(n_seg), dim3(kSelThreads), 0, stream, wsum,     \
                        len, first, last, flags, n_units, budget, recent, score, keep,           \
-                       kept_tokens, status);
+                       kept_tokens, status);                                                    \
+  else
   OMNITIDE_SELECT_CASE(1)
   OMNITIDE_SELECT_CASE(2)
   OMNITIDE_SELECT_CASE(4)
   OMNITIDE_SELECT_CASE(8)
 #undef OMNITIDE_SELECT_CASE
-  else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-"""Selection beyond 512 units (the workgroup radix select): unit counts at the edges of the
-units-per-thread steps, with candidate keys that agree in their high bits, are all equal, or span
+"""Selection at the edges of its dispatch (one wave with one or two units per lane, a workgroup with
+one, two, four or eight per thread), with candidate keys that agree in their high bits, are all equal, or span
 the whole key range, and budgets from nothing to everything, against the oracle."""
 import numpy as np
 import pytest
@@ -27,12 +27,14 @@ def _scores(kind, rng, U):
     return np.floor(2.0 ** rng.uniform(0, 49, size=U)).astype(np.int64)     # every key length
 
 
-@pytest.mark.parametrize("U", [513, 1024, 1025, 4096, 8191, 8192])
+@pytest.mark.parametrize("U", [1, 63, 64, 65, 128, 129, 512, 1024, 1025, 2049, 4096, 8191,
+                               8192])
 @pytest.mark.parametrize("kind", ["clustered", "equal", "wide"])
-def test_wide_select_matches_oracle(U, kind):
+def test_select_matches_oracle(U, kind):
     from paper_2609_34653_amd import omnitide as ot
     rng = np.random.default_rng(U + len(kind))
     lens = rng.integers(0, 60, size=U)
+    lens[0] = 5
     end = np.cumsum(lens)
     first = np.where(lens > 0, end - lens, 10 ** 7)
     last = np.where(lens > 0, end - 1, -1)
@@ -44,6 +46,7 @@ def test_wide_select_matches_oracle(U, kind):
     # nothing beyond the prefix, one candidate's worth, a part, all but one token, everything
     for budget, recent in ((sysn, 0), (sysn + 25, 0), (total // 3, 300), (total - 1, 0),
                            (total, total), (total, 100)):
+        budget = max(budget, sysn)            # the prefix always fits
         sc = torch.full((U,), -7, dtype=torch.int64, device="cuda")
         keep = torch.full((U,), 9, dtype=torch.uint8, device="cuda")
         kept = torch.full((1,), -7, dtype=torch.int32, device="cuda")
