@@ -4,9 +4,9 @@
 //   evict_plan     one workgroup per segment: scans over units give each unit its first
 //                  logical position (exclusive sum of lengths), kept length, deleted tokens
 //                  before it and new id; the table goes to the workspace.
-//   evict_apply    one thread per slot: rewrites the tags in place (kept: new id, position minus
+//   evict_apply    four slots per thread: rewrites the tags in place (kept: new id, position minus
 //                  the deleted tokens before its unit; otherwise empty); the span (last occupied
-//                  slot + 1) is a per-wave maximum published with one atomic per wave.
+//                  slot + 1) is a maximum over the workgroup's 1,024 slots, raised by one atomic.
 //   The single-workgroup scans below first pack the segment's occupancy into an LDS bitmap
 //   (one bit per slot, all loads in flight at once), then work on bits: counts are popcounts
 //   and "last occupied slot" is a bit scan.
@@ -41,22 +41,28 @@ struct UnitRec {
   int32_t rank;   // new id, -1 when dropped
 };
 
+// Bound by latency and by the instructions of one workgroup, so the units per thread are a template
+// argument and the three scans share one barrier: eviction of a 9,000-slot pool in 40 units 6.9 us
+// with four block scans and eight units' code per thread, 5.5 so.
+template <int PER>
 __global__ __launch_bounds__(kNatThreads) void evict_plan_kernel(
     const uint8_t* __restrict__ keep_g, const int32_t* __restrict__ keep_len_g,
     const int32_t* __restrict__ len_g, int n_units, UnitRec* __restrict__ table,
     int32_t* __restrict__ remap_g, int32_t* __restrict__ kept_g,
     int32_t* __restrict__ n_kept_units_g, int32_t* __restrict__ span_g) {
-  __shared__ int32_t scr[kNatThreads / kWave + 1];
+  constexpr int kWaves = kNatThreads / kWave;
+  static_assert(kWaves == 16, "wave totals are read by lanes 0..15");
+  __shared__ int4 totals[kWaves];
   const int seg = blockIdx.x;
   const int tid = threadIdx.x;
   const int U = n_units;
   const int per = (U + kNatThreads - 1) / kNatThreads;
   const int u0 = tid * per;
   const size_t base = static_cast<size_t>(seg) * U;
-  int ln[kNatPer], kl[kNatPer];
-  int my_len = 0, my_kept = 0, my_del = 0, my_n = 0;
+  int ln[PER], kl[PER];
+  int my_len = 0, my_kept = 0, my_n = 0;
 #pragma unroll
-  for (int i = 0; i < kNatPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     ln[i] = kl[i] = 0;
     if (i < per && u < U) {
@@ -66,16 +72,26 @@ __global__ __launch_bounds__(kNatThreads) void evict_plan_kernel(
     }
     my_len += ln[i];
     my_kept += kl[i];
-    my_del += ln[i] - kl[i];
     my_n += kl[i] > 0 ? 1 : 0;
   }
-  int total_len, kept, dropped, n_kept;
-  int pos0 = block_exclusive_scan(my_len, scr, &total_len);
-  int del = block_exclusive_scan(my_del, scr, &dropped);
-  int rk = block_exclusive_scan(my_n, scr, &n_kept);
-  (void)block_exclusive_scan(my_kept, scr, &kept);
+  // the three scans together: wave scans, the waves' totals, one barrier
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int inc_len = wave_inclusive_scan(my_len), inc_kept = wave_inclusive_scan(my_kept),
+            inc_n = wave_inclusive_scan(my_n);
+  if (lane == kWave - 1) totals[wave] = make_int4(inc_len, inc_kept, inc_n, 0);
+  __syncthreads();
+  // lane l < 16 holds wave l's totals
+  const int4 t = lane < kWaves ? totals[lane & (kWaves - 1)] : make_int4(0, 0, 0, 0);
+  const bool before = lane < wave;
+  auto sum = [](int v) { return static_cast<int>(wave_sum_u32(static_cast<uint32_t>(v))); };
+  int pos0 = sum(before ? t.x : 0) + inc_len - my_len;
+  const int kept0 = sum(before ? t.y : 0) + inc_kept - my_kept;
+  int rk = sum(before ? t.z : 0) + inc_n - my_n;
+  int del = pos0 - kept0;                          // deleted = length - kept, unit by unit
+  const int kept = sum(t.y), n_kept = sum(t.z);
 #pragma unroll
-  for (int i = 0; i < kNatPer; ++i) {
+  for (int i = 0; i < PER; ++i) {
     const int u = u0 + i;
     if (i < per && u < U) {
       const int r = kl[i] > 0 ? rk++ : -1;
@@ -129,43 +145,69 @@ __device__ inline void load_bitmap(const uint32_t* __restrict__ bits_g, uint32_t
   }
   __syncthreads();
 }
+
 // shift_g (optional, [n_seg][cap]): each slot's position change (0 for slots that are empty,
 // evicted or keep their position), for the rotary adjustment of the keys that stay.
+// A workgroup takes kApplySlots consecutive slots, kApplyPer per thread with their loads in flight
+// together, and raises the span once: atomics on one word run one after another, and with one per
+// wave of 64 slots the eviction of a pool of 98,969 slots that keeps them all took 21.7 us, 5.9 so.
+constexpr int kApplyPer = 4;
+constexpr int kApplySlots = kCopyThreads * kApplyPer;
+
 __global__ __launch_bounds__(kCopyThreads) void evict_apply_kernel(
     int32_t* __restrict__ uid_g, int32_t* __restrict__ pos_g, int cap, int n_units,
     const UnitRec* __restrict__ table, const int32_t* __restrict__ len_g,
     int32_t* __restrict__ span_g, int32_t* __restrict__ shift_g, int32_t* __restrict__ status) {
+  __shared__ int32_t ends[kCopyThreads / kWave];
   const int seg = blockIdx.y;
-  const int s = blockIdx.x * kCopyThreads + threadIdx.x;
+  const int tid = threadIdx.x;
+  const int s0 = blockIdx.x * kApplySlots + tid;
   const size_t sb = static_cast<size_t>(seg) * cap;
   const size_t ub = static_cast<size_t>(seg) * n_units;
-  int end = 0;                                    // slot + 1 if this slot stays occupied
-  if (s < cap) {
-    const int u = uid_g[sb + s];
+  int u[kApplyPer], p[kApplyPer], n[kApplyPer];
+  UnitRec rec[kApplyPer];
+#pragma unroll
+  for (int i = 0; i < kApplyPer; ++i) {
+    const int s = s0 + i * kCopyThreads;
+    u[i] = s < cap ? uid_g[sb + s] : -1;
+    p[i] = s < cap ? pos_g[sb + s] : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < kApplyPer; ++i) {          // some unit's record for slots without one
+    const int c = min(max(u[i], 0), n_units - 1);
+    rec[i] = table[ub + c];
+    n[i] = len_g[ub + c];
+  }
+  int end = 0;                                   // last occupied slot + 1
+#pragma unroll
+  for (int i = 0; i < kApplyPer; ++i) {
+    const int s = s0 + i * kCopyThreads;
+    if (s >= cap) continue;
     int shift = 0;
-    if (u >= 0) {
-      bool bad = u >= n_units;
-      if (!bad) {
-        const UnitRec rec = table[ub + u];
-        const int p = pos_g[sb + s];
-        const int r = p - rec.pos0;               // rank of the token inside its unit
-        bad = r < 0 || r >= len_g[ub + u];
-        if (!bad && r < rec.kl) {
-          uid_g[sb + s] = rec.rank;
-          pos_g[sb + s] = p - rec.del;
-          shift = -rec.del;
-          end = s + 1;
-        } else if (!bad) {
-          uid_g[sb + s] = -1;
-          pos_g[sb + s] = -1;
-        }
+    if (u[i] >= 0) {
+      const int r = p[i] - rec[i].pos0;          // rank of the token inside its unit
+      if (u[i] >= n_units || r < 0 || r >= n[i]) {
+        set_status(status, OMNITIDE_E_TAGS);
+      } else if (r < rec[i].kl) {
+        uid_g[sb + s] = rec[i].rank;
+        pos_g[sb + s] = p[i] - rec[i].del;
+        shift = -rec[i].del;
+        end = s + 1;
+      } else {
+        uid_g[sb + s] = -1;
+        pos_g[sb + s] = -1;
       }
-      if (bad) set_status(status, OMNITIDE_E_TAGS);
     }
     if (shift_g != nullptr) shift_g[sb + s] = shift;
   }
   end = wave_max_i32(end);
-  if ((threadIdx.x & (kWave - 1)) == 0 && end > 0) atomicMax(span_g + seg, end);
+  if ((tid & (kWave - 1)) == 0) ends[tid / kWave] = end;
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < kCopyThreads / kWave; ++w) end = max(end, ends[w]);
+    if (end > 0) atomicMax(span_g + seg, end);
+  }
 }
 
 __global__ __launch_bounds__(kNatThreads) void suffix_plan_kernel(
@@ -470,9 +512,17 @@ size_t evict_rope_workspace_bytes(int n_seg, int n_units, int cap) {
 
 hipError_t launch_evict(const EvictArgs& a, hipStream_t stream) {
   UnitRec* table = static_cast<UnitRec*>(a.workspace);
-  hipLaunchKernelGGL(evict_plan_kernel, dim3(a.n_seg), dim3(kNatThreads), 0, stream, a.keep,
-                     a.keep_len, a.unit_len, a.n_units, table, a.unit_remap, a.kept_tokens,
-                     a.n_kept_units, a.span);
+#define OMNITIDE_EVICT_PLAN(PER)                                                                \
+  if (a.n_units <= PER * kNatThreads)                                                          \
+    hipLaunchKernelGGL(evict_plan_kernel<PER>, dim3(a.n_seg), dim3(kNatThreads), 0, stream,    \
+                       a.keep, a.keep_len, a.unit_len, a.n_units, table, a.unit_remap,         \
+                       a.kept_tokens, a.n_kept_units, a.span);                                 \
+  else
+  OMNITIDE_EVICT_PLAN(1)
+  OMNITIDE_EVICT_PLAN(2)
+  OMNITIDE_EVICT_PLAN(kNatPer)
+    return hipErrorInvalidValue;
+#undef OMNITIDE_EVICT_PLAN
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.cap == 0) return hipSuccess;
@@ -481,7 +531,7 @@ hipError_t launch_evict(const EvictArgs& a, hipStream_t stream) {
                                          static_cast<uint8_t*>(a.workspace) +
                                          align256(evict_workspace_bytes(a.n_seg, a.n_units)))
                                    : nullptr;
-  const dim3 grid((a.cap + kCopyThreads - 1) / kCopyThreads, a.n_seg);
+  const dim3 grid((a.cap + kApplySlots - 1) / kApplySlots, a.n_seg);
   hipLaunchKernelGGL(evict_apply_kernel, grid, dim3(kCopyThreads), 0, stream, a.unit_id, a.pos,
                      a.cap, a.n_units, table, a.unit_len, a.span, shift, a.d_status);
   e = hipGetLastError();

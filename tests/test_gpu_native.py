@@ -791,3 +791,34 @@ def check_decode(outs, qd, o, span, q_pos0, scale):
 def bf16_view(a):
     """Storage values (uint16 bf16 bit patterns) as a CPU bf16 tensor."""
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).view(torch.bfloat16)
+
+
+@pytest.mark.parametrize("U,cap", [(1, 1023), (1024, 1025), (1025, 5000), (2048, 4096),
+                                   (2049, 6143), (8192, 20000)])
+@pytest.mark.parametrize("keep_all", [False, True])
+def test_evict_native_dispatch_edges(U, cap, keep_all):
+    """Unit counts at the edges of the plan's units per thread, pools around a workgroup's 1,024
+    slots, entries in any physical order, kept prefixes of any length (none and all included)."""
+    from paper_2609_34653_amd import omnitide as ot
+    rng = np.random.default_rng(U + cap)
+    length = rng.integers(0, 2 * max(1, cap // (2 * U)) + 1, size=U)
+    length[-1] = max(0, min(length[-1], cap - int(length[:-1].sum())))
+    n = int(length.sum())
+    assert n <= cap
+    slots = rng.permutation(cap)[:n]
+    uid, pos = np.full(cap, -1, np.int32), np.full(cap, -1, np.int32)
+    uid[slots], pos[slots] = np.repeat(np.arange(U), length), np.arange(n)
+    kl = length if keep_all else rng.integers(-1, 1 + 2 * length.clip(1))
+    ev = oracle.evict_logical(uid, pos, np.clip(kl, 0, length), U)
+    t_uid, t_pos, remap = i32(uid), i32(pos), i32(np.full(U, -7))
+    kept, nku, span, st = i32([-7]), i32([-7]), i32([-7]), i32([0])
+    ws = torch.full((ot.omnitide_evict_native_workspace_bytes(1, U),), 0xFF, dtype=torch.uint8,
+                    device="cuda")
+    ot.omnitide_evict_native(t_uid, t_pos, 1, U, i32(length), remap, kept, nku, span, ws,
+                             keep_len=i32(kl), d_status=st)
+    torch.cuda.synchronize()
+    assert int(host(st)[0]) == 0
+    assert np.array_equal(host(t_uid), ev["unit_id"]) and np.array_equal(host(t_pos), ev["pos"])
+    assert np.array_equal(host(remap), ev["unit_remap"])
+    assert int(host(kept)[0]) == ev["kept"] and int(host(nku)[0]) == ev["n_kept_units"]
+    assert int(host(span)[0]) == oracle.span_of(ev["unit_id"])
