@@ -255,8 +255,8 @@ size_t omnitide_compact_workspace_bytes(int n_seg, int n_units, int cap_dst);
  *                [0, n_slots), runs are out of unit order, or a unit holds a modality > 4;
  *                the segment's keep_len and keep_slot are then all 0 and kept_tokens 0.
  * Limits: 1 <= n_units <= 8192, n_slots >= 0, 0 <= low_watermark <= high_watermark, and
- * recent_tokens, sink_video, sink_audio, text_budget >= 0.  Three kernels: a census of each
- * unit's spans (one wave per unit), the plan (one workgroup per segment), the slot mask.
+ * recent_tokens, sink_video, sink_audio, text_budget >= 0.  A census of each unit's spans (one
+ * wave per unit), then the plan and the slot mask (one kernel up to 512 units, two beyond).
  */
 int omnitide_plan_spans(const int32_t* unit_len, const int32_t* unit_first_slot,
                         const int32_t* unit_last_slot, const uint32_t* unit_flags,
@@ -308,8 +308,8 @@ int omnitide_compact_kv_spans(const void* k_src, const void* v_src, int dtype, i
  *   k, v   [n_seg][cap][n_kv_heads][head_dim] of `dtype`: the pools written by
  *          omnitide_compact_kv (the chunk's own keys are the last chunk_len rows before n_ctx)
  *   dtype  OMNITIDE_BF16, or OMNITIDE_F32: q, k and v are then rounded to bf16 (nearest even)
- *          into the workspace first (all cap rows of k and v), and the bf16 kernels run on
- *          the copies
+ *          into the workspace first (the rows of k and v below n_ctx), and the bf16 kernels
+ *          run on the copies
  *   n_ctx  int32 [n_seg], device: rows in use; chunk_len <= n_ctx <= cap is required (device
  *          check: OMNITIDE_E_CAPACITY, the segment's output is then not written)
  *   out    [n_seg][chunk_len][n_q_heads][head_dim] of `out_dtype`: OMNITIDE_F32, or

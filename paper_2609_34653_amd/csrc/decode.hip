@@ -8,9 +8,9 @@
 // per-key dot products, their cross-lane reductions and the P*V updates cost as much time as the
 // loads themselves, while a 16x16 MFMA block with the query vectors as columns (half of them
 // padding) costs almost nothing.
-//   grid      (key split, KV head, segment); the split count is chosen so that about 256
-//             eight-wave workgroups run (one per CU), and a combine kernel merges the partials in
-//             split order.
+//   grid      (key split, KV head, segment), eight-wave workgroups, one resident per CU; the split
+//             count fills whole rounds of 256 (decode_num_splits), and a combine kernel merges the
+//             partials in split order.
 //   waves     each wave owns 16 keys of every 128-key workgroup step and loads the next step's
 //             keys before it works on the current ones: the K operands straight from global
 //             memory into registers, the V rows by direct loads into a private double buffer in
