@@ -315,7 +315,9 @@ int omnitide_compact_kv_spans(const void* k_src, const void* v_src, int dtype, i
  *   out    [n_seg][chunk_len][n_q_heads][head_dim] of `out_dtype`: OMNITIDE_F32, or
  *          OMNITIDE_BF16 (the float result rounded to nearest even)
  *   workspace  device scratch of omnitide_attn_workspace_bytes(dtype, ...) bytes (split-KV
- *          partials, and the bf16 copies for float32 inputs; may be NULL when that is 0)
+ *          partials, and the bf16 copies for float32 inputs; may be NULL when that is 0).  The
+ *          size never falls as cap grows, so a workspace sized for the largest pool serves
+ *          smaller ones (all other arguments equal)
  * Numerics: bf16 inputs, bf16 matrix-core products with fp32 accumulation, fp32 softmax.
  * Limits: head_dim in {64, 128}; n_q_heads % n_kv_heads == 0; chunk_len >= 1; cap >= chunk_len.
  */
@@ -454,7 +456,8 @@ size_t omnitide_place_chunk_workspace_bytes(int n_seg, int cap);
  *   q, k, v, out, scale: as omnitide_chunk_attn.  The K/V bytes of empty slots are never used
  *   (they may hold anything, NaN included).
  *   q, k, v are bf16 and out float32 (OMNITIDE_E_DTYPE is not used here).
- *   workspace  device scratch of omnitide_span_attn_workspace_bytes() bytes (always > 0).
+ *   workspace  device scratch of omnitide_span_attn_workspace_bytes() bytes (always > 0; never
+ *            falls as cap grows).
  * traversal -- which slots the kernel visits (the result is the same up to summation order):
  *   OMNITIDE_SPAN_FULL        every 64-slot tile of the span, masked (a kernel presented the
  *                             physical span);

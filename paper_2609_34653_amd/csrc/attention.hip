@@ -44,11 +44,7 @@ constexpr int kKT = 64;                  // keys per tile
 constexpr int kRowsWG = kAttnWaves * 32; // query rows per workgroup
 constexpr int kNumXcd = 8;
 constexpr int kNumCU = 256;
-constexpr long kMaxSplits = 16;          // key splits of a call at most
-// A call's split partials at most: two full row tiles per CU at d = 128.  They fit the fixed
-// scratch of the allocation-free call, so it takes every shape.
-constexpr double kMaxPartialBytes = 2. * kNumCU * kRowsWG * (128 + 2) * sizeof(float);
-static_assert(kMaxPartialBytes <= OMNITIDE_NOALLOC_SCRATCH_BYTES, "partials exceed the scratch");
+constexpr int kTargetWGs = 2 * kNumCU;   // two resident workgroups on each CU
 
 // LDS layout: two K and two V tile buffers, each row-major [64 keys][D]:
 //   K  16-byte chunks XOR-swizzled by kswz(key), so the 8 (and 16) lanes one LDS cycle serves
@@ -825,48 +821,65 @@ hipError_t launch_attn_t(const AttnArgs& a, int n_split, hipStream_t stream) {
 
 }  // namespace
 
-// Key splits of a call, by its estimated time in microseconds (d = 128; a tile of d = 64 takes 0.63
-// of one of d = 128).  A CU with one workgroup takes about 1.0 us per 64-key tile and with two
-// resident ones 0.85 per tile of each, and a workgroup's start and drain cost about two tiles
-// more; beyond 512 workgroups the grid runs in rounds.  Splitting adds the combine's launch and
-// the partials, written once and read once, and the output at about 8 TB/s together.  Measured over 22
-// shapes with rotating inputs the choice is 1.4% from the best split on average where filling 512
-// workgroups whatever the length was 5% (1,024 queries over 1,024 keys, 32/8 heads: 33.7 us with
-// two splits, 25.4 with one; 665 over 1,500: 34.4 with three, 32.4 with one; 89 over 601, 4/1 heads, d = 64:
-// 10.8 with two, 9.2 with ten).
+// Key splits of a call at most, and what its workspace is for: as many as fill kTargetWGs
+// workgroups with at least four tiles each, which grows with the pool, so a workspace sized for a
+// pool is enough for every smaller one.
+static int attn_max_splits(int n_seg, int cap, int chunk_len, int n_q_heads, int n_kv_heads) {
+  const int G = n_q_heads / n_kv_heads;
+  const long n_mt = (static_cast<long>(chunk_len) * G + kRowsWG - 1) / kRowsWG;
+  const long base = n_mt * n_kv_heads * n_seg;
+  const long tiles = (static_cast<long>(cap) + kKT - 1) / kKT;
+  return static_cast<int>(std::max(1L, std::min({kTargetWGs / base, tiles / 4, 16L})));
+}
+
+// Key splits of a call: the most (above), or the fewer whose estimated time is least where that
+// saves 15% (fewer partials to write and merge; a CU left with one workgroup runs it faster).
+// Estimate in microseconds: a CU with one workgroup takes 1.0 per 64-key tile (0.65 at d = 64),
+// with two 1.6 for a tile of each (1.04); start and drain of a workgroup cost two tiles; the
+// launches 5.5 and the combine's 3.0; the partials, written once and read once, and the output
+// run at 5.8 TB/s.  It is within 8% (one standard deviation) of the times of 1,039 random shapes
+// (1-24 segments, 16-2,400 queries over 600-40,000 keys) under every split count.  There the rule is
+// 1.3% faster than the most splits on average, 1.43x at best, and never slower by more than 1.5%,
+// also where the context is a half or a quarter of the pool; with a 12% margin one shape was 1.6%
+// slower, and an estimate that could also ask for more splits or went by the least time alone made
+// 77 of them up to 16% slower (18 x 103 queries, 8/8 heads, d = 64, 12,824 keys: 105 us with the most,
+// three, 124 with seven).  1,024 queries over 1,024 keys, 32/8 heads: 35.5 us with two, 26.8 with one.
 int attn_num_splits(int n_seg, int cap, int chunk_len, int n_q_heads, int n_kv_heads,
                     int head_dim) {
   const int G = n_q_heads / n_kv_heads;
   const long n_mt = (static_cast<long>(chunk_len) * G + kRowsWG - 1) / kRowsWG;
   const long base = n_mt * n_kv_heads * n_seg;
-  const long tiles = (static_cast<long>(cap) + kKT - 1) / kKT;
+  const double tiles = static_cast<double>((static_cast<long>(cap) + kKT - 1) / kKT);
   const double rows = static_cast<double>(n_seg) * chunk_len * n_q_heads;
   const double part_bytes = rows * (head_dim + 2) * sizeof(float);    // of one split
-  const double tile_us = head_dim == 128 ? 1. : 0.63;
-  int best = 1;
-  double best_us = 0.;
-  for (long s = 1; s <= std::min<long>(tiles, kMaxSplits); ++s) {
-    if (s > 1 && static_cast<double>(s) * part_bytes > kMaxPartialBytes) break;
-    const long wgs = base * s;
-    const double per_tile = wgs <= kNumCU       ? 1.
-                            : wgs <= 2 * kNumCU ? 2 * 0.85
-                                                : 0.85 * ((wgs + kNumCU - 1) / kNumCU);
-    const double us = per_tile * tile_us * static_cast<double>((tiles + s - 1) / s + 2) +
-                      (s == 1 ? 0. : 3. + part_bytes * static_cast<double>(2 * s + 1) / 8e6);
-    if (s == 1 || us < best_us) {
-      best = static_cast<int>(s);
+  const double one_us = head_dim == 128 ? 1. : 0.65;
+  auto estimate = [&](int s) {
+    const double tile_us = base * s <= kNumCU ? one_us : 1.6 * one_us;
+    return 5.5 + tile_us * (tiles / s + 2.) + (s == 1 ? 0. : 3. + part_bytes * (2 * s + 1) / 5.8e6);
+  };
+  const int most = attn_max_splits(n_seg, cap, chunk_len, n_q_heads, n_kv_heads);
+  int best = most;
+  double best_us = 0.85 * estimate(most);
+  for (int s = 1; s < most; ++s) {
+    const double us = estimate(s);
+    if (us < best_us) {
+      best = s;
       best_us = us;
     }
   }
   return best;
 }
 
+static size_t partial_bytes(int n_split, int n_seg, int chunk_len, int n_q_heads, int head_dim) {
+  const size_t rows = static_cast<size_t>(n_seg) * chunk_len * n_q_heads;
+  return n_split == 1 ? 0 : static_cast<size_t>(n_split) * rows *
+                                (static_cast<size_t>(head_dim) + 2) * sizeof(float);
+}
+
 size_t attn_workspace_bytes(int n_seg, int cap, int chunk_len, int n_q_heads, int n_kv_heads,
                             int head_dim) {
-  const int s = attn_num_splits(n_seg, cap, chunk_len, n_q_heads, n_kv_heads, head_dim);
-  if (s == 1) return 0;
-  const size_t rows = static_cast<size_t>(n_seg) * chunk_len * n_q_heads;
-  return static_cast<size_t>(s) * rows * (static_cast<size_t>(head_dim) + 2) * sizeof(float);
+  return partial_bytes(attn_max_splits(n_seg, cap, chunk_len, n_q_heads, n_kv_heads), n_seg,
+                       chunk_len, n_q_heads, head_dim);
 }
 
 size_t span_attn_workspace_bytes(int n_seg, int cap, int chunk_len, int n_q_heads,
@@ -960,6 +973,12 @@ hipError_t launch_attn(const AttnArgs& a, hipStream_t stream) {
 // kernel (on the host it is only a stand-in for the symbol): the device address comes from
 // hipGetSymbolAddress, taken once per device with that device current, and is cached here.
 static __device__ __align__(256) uint8_t scratch[OMNITIDE_NOALLOC_SCRATCH_BYTES];
+// Splits times row-tile workgroups never exceed kTargetWGs and a row tile holds kRowsWG rows, so
+// the partials need at most kTargetWGs * kRowsWG * (128 + 2) floats: every valid shape fits.
+static_assert(static_cast<size_t>(kTargetWGs) * kRowsWG * (128 + 2) * sizeof(float) <=
+                  OMNITIDE_NOALLOC_SCRATCH_BYTES,
+              "the most splits can exceed the fixed scratch");
+
 namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

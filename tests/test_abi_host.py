@@ -282,8 +282,8 @@ def test_attention_noalloc_validation(L):
 
 
 def test_noalloc_scratch_covers_every_shape():
-    """Splits times row-tile workgroups stay within 512, so the partials of any shape fit the
-    fixed 64 MiB array (the E_SCRATCH check is a guard, not a reachable limit today)."""
+    """Splits times row-tile workgroups of 128 rows stay within 512, so the partials of any shape
+    fit the fixed 64 MiB array (the E_SCRATCH check is a guard, not a reachable limit today)."""
     worst = 0
     for n_seg in (1, 2, 3, 8, 36):
         for Lc in (1, 32, 89, 128, 665, 1000, 2329, 8192):
@@ -295,6 +295,33 @@ def test_noalloc_scratch_covers_every_shape():
                         worst = max(worst, ot.omnitide_attn_workspace_bytes(n_seg, cap, Lc, Hq,
                                                                             Hkv, d))
     assert 0 < worst <= 512 * 128 * 130 * 4 <= ot.NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("Lc,Hq,Hkv,d,n_seg", [(16, 32, 8, 128, 1), (89, 4, 1, 64, 1),
+                                                 (331, 14, 2, 64, 1), (665, 32, 8, 128, 1),
+                                                 (1024, 32, 8, 128, 1), (103, 8, 8, 64, 18)])
+def test_attention_workspace_serves_smaller_pools(L, Lc, Hq, Hkv, d, n_seg):
+    """One workspace sized for a pool is enough for every smaller pool (the overlap of out and k,
+    checked after the workspace, ends each call here before anything is launched)."""
+    kw = dict(n_seg=n_seg, Lc=Lc, Hq=Hq, Hkv=Hkv, d=d, out=fake(1))
+    need = 0
+    for cap in range(Lc, 40 * 1024, 61):
+        n = ot.omnitide_attn_workspace_bytes(n_seg, cap, Lc, Hq, Hkv, d)
+        assert n >= need, cap
+        need = n
+        assert attn(L, cap=cap, wsb=need, **kw) == ot.E_ALIAS
+    for cap in range(Lc, 40 * 1024, 611):
+        assert attn(L, cap=cap, wsb=need, **kw) == ot.E_ALIAS, cap
+
+
+@pytest.mark.parametrize("Lc,cap,Hq,Hkv,d,n_seg", [(89, 448, 4, 1, 64, 1), (64, 448, 8, 1, 128, 1),
+                                                   (1029, 9000, 32, 8, 128, 1),
+                                                   (397, 33768, 14, 2, 64, 6)])
+def test_attention_without_workspace(L, Lc, cap, Hq, Hkv, d, n_seg):
+    """Pools under eight tiles, and calls of more than 256 row-tile workgroups, need none."""
+    assert ot.omnitide_attn_workspace_bytes(n_seg, cap, Lc, Hq, Hkv, d) == 0
+    assert attn(L, n_seg=n_seg, cap=cap, Lc=Lc, Hq=Hq, Hkv=Hkv, d=d, ws=None, wsb=0,
+                out=fake(1)) == ot.E_ALIAS
 
 
 def span_attn(L, **kw):
@@ -417,7 +444,6 @@ def test_decode_validation(L):
     assert decode(L, out=P(fake(1).value + 64)) == ot.E_ALIAS
     assert ot.omnitide_decode_workspace_bytes(1, 1000, 1, 32, 8, 128) > 0
     assert ot.omnitide_decode_workspace_bytes(1, 1000, 1, 30, 8, 128) == 0
-
 
 
 def decode_span(L, **kw):

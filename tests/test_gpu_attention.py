@@ -30,9 +30,10 @@ def bf16(a):
     return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(torch.bfloat16)
 
 
-def run_attn(q, k, v, n_ctx, scale):
+def run_attn(q, k, v, n_ctx, scale, splits=None):
     """q [n_seg, L, Hq, d], k/v [n_seg, cap, Hkv, d] (bf16, host); returns out [n_seg, L, Hq, d]
-    float32 and the device status."""
+    float32 and the device status.  splits: the key splits the call is expected to use, i.e. the
+    partials (d + 2 floats per row and split) it leaves in a workspace filled with 0xFF."""
     from paper_2609_34653_amd import omnitide as ot
     n_seg, L, Hq, d = q.shape
     cap, Hkv = k.shape[1], k.shape[2]
@@ -44,6 +45,9 @@ def run_attn(q, k, v, n_ctx, scale):
                            torch.tensor(n_ctx, dtype=torch.int32, device="cuda"), scale, out, ws,
                            st)
     torch.cuda.synchronize()
+    if splits is not None:
+        written = int((ws[:nb].view(torch.int32) != -1).sum())
+        assert written == (splits * n_seg * L * Hq * (d + 2) if splits > 1 else 0)
     return out.cpu().numpy(), int(st.item())
 
 
@@ -117,7 +121,8 @@ def run_attn_dtypes(q, k, v, n_ctx, scale, out_dtype):
 
 @pytest.mark.parametrize("n_ctx,cap,L,Hq,Hkv,d", [
     ([17048], 17100, 665, 32, 8, 128),        # the 80K-history shape: three splits, combine
-    ([700, 300], 800, 37, 8, 2, 64),          # two segments, one split
+    ([700, 300], 800, 37, 8, 2, 64),          # two segments, three splits
+    ([300, 200], 300, 37, 8, 2, 64),          # two segments, one split
 ])
 def test_output_and_input_dtypes(n_ctx, cap, L, Hq, Hkv, d):
     """bf16 output: the float32 result rounded to nearest even, bit for bit (single-split and
@@ -167,19 +172,24 @@ def test_float32_rows_past_context_and_bad_segment():
         check(out[i].numpy(), *(t[i].to(torch.bfloat16) for t in (q, k, v)), n, d ** -0.5)
 
 
-@pytest.mark.parametrize("n_ctx,cap,L,Hq,Hkv,d", [
-    ([601], 601, 89, 4, 1, 64),           # one or two tiles per split
-    ([100], 4000, 64, 8, 1, 128),         # the context ends in the first splits: the rest are empty
-    ([1024], 1024, 1024, 8, 8, 64),       # no history, unsplit
-    ([64, 2000], 2100, 33, 8, 2, 128),    # a one-tile segment beside a long one
+@pytest.mark.parametrize("n_ctx,cap,L,Hq,Hkv,d,splits", [
+    ([601], 601, 89, 4, 1, 64, 2),            # the most: at least four tiles each
+    ([100], 4000, 64, 8, 1, 128, 15),         # the context ends in the first splits: the rest are empty
+    ([1024], 1024, 1024, 8, 8, 64, 4),        # no history
+    ([64, 2000], 2100, 33, 8, 2, 128, 8),     # a one-tile segment beside a long one
+    ([1024], 1024, 1024, 32, 8, 64, 1),       # unsplit where two splits fill the chip
+    ([650], 700, 650, 32, 8, 128, 1),
+    ([1600], 1600, 200, 32, 8, 128, 4),       # four where six fill the chip
+    ([200], 300, 37, 8, 2, 64, 1),            # too short to split
 ])
-def test_split_choice_edges(n_ctx, cap, L, Hq, Hkv, d):
-    """Splits of one tile, empty splits and unsplit calls, with a NaN-filled workspace."""
+def test_split_choice_edges(n_ctx, cap, L, Hq, Hkv, d, splits):
+    """Empty splits, fewer splits than fill the chip and unsplit calls, with a NaN-filled
+    workspace."""
     rng = np.random.default_rng(cap + L)
     n_seg = len(n_ctx)
     q = bf16(rng.standard_normal((n_seg, L, Hq, d)))
     k, v = (bf16(rng.standard_normal((n_seg, cap, Hkv, d))) for _ in range(2))
-    out, status = run_attn(q, k, v, n_ctx, d ** -0.5)
+    out, status = run_attn(q, k, v, n_ctx, d ** -0.5, splits)
     assert status == 0
     for i, n in enumerate(n_ctx):
         check(out[i], q[i], k[i], v[i], n, d ** -0.5)
