@@ -501,8 +501,11 @@ size_t omnitide_span_attn_workspace_bytes(int n_seg, int cap, int chunk_len, int
  *   n_ctx        int32 [n_seg] device; n_q <= n_ctx <= cap, else OMNITIDE_E_CAPACITY on the
  *                device and that segment's output is not written
  *   out          float32 [n_seg][n_q][n_q_heads][head_dim]
- *   workspace    device scratch of omnitide_decode_workspace_bytes() bytes (may be NULL when
- *                that is 0): split partials
+ *   workspace    device scratch of omnitide_decode_workspace_bytes() bytes: split partials.  The
+ *                size never falls as cap grows.  Less is accepted (and may cost time) down to
+ *                the partials of s = min(256 / (n_seg * n_kv_heads), ceil(cap / 64), 128)
+ *                splits, s * n_seg * n_q * n_q_heads * (head_dim + 2) floats, or NULL where
+ *                s <= 1 (more than 128 (segment, KV head) pairs, or cap <= 64)
  * Arithmetic: bf16 inputs, float dot products, softmax and accumulation (probabilities are not
  * rounded).  Bandwidth-bound: each (key, KV head) row is read once per call.
  * Limits: n_q * (n_q_heads / n_kv_heads) <= 8, head_dim in {64, 128}, scale finite.
@@ -534,7 +537,9 @@ size_t omnitide_decode_workspace_bytes(int n_seg, int cap, int n_q, int n_q_head
  *            the output is unspecified; host limit cap * n_kv_heads * head_dim * 2 < 2^32);
  *            other values: OMNITIDE_E_SHAPE.
  *   q, k, v, out, scale, arithmetic and limits: as omnitide_decode_attn; cap <= 2,097,152.
- *   workspace  device scratch of omnitide_decode_span_workspace_bytes() bytes (always > 0).
+ *   workspace  device scratch of omnitide_decode_span_workspace_bytes() bytes (always > 0).  The
+ *            size never falls as cap grows, and as much less is accepted as by
+ *            omnitide_decode_attn.
  * With key_pos[j] = j for j < span and q_pos0 = span - n_q this computes omnitide_decode_attn
  * with n_ctx = span (up to summation order).
  */

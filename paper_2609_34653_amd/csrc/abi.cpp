@@ -678,7 +678,8 @@ size_t omnitide_decode_workspace_bytes(int n_seg, int cap, int n_q, int n_q_head
   if (n_seg < 1 || cap < 1 || n_q < 1 || n_kv_heads < 1 || n_q_heads < n_kv_heads ||
       n_q_heads % n_kv_heads != 0 || !(head_dim == 64 || head_dim == 128))
     return 0;
-  return omnitide::decode_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads, head_dim);
+  return omnitide::decode_workspace_bytes(false, n_seg, cap, n_q, n_q_heads, n_kv_heads,
+                                          head_dim);
 }
 
 namespace {
@@ -701,14 +702,17 @@ int decode_impl(const void* q, const void* k, const void* v, const int32_t* n_ct
   // position order gathers V rows by 32-bit byte offsets from the segment's base
   if (pos_order && static_cast<size_t>(cap) * n_kv_heads * head_dim * 2 > 0xffffffffull)
     return OMNITIDE_E_SHAPE;
-  const size_t need =
-      span ? omnitide::decode_span_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads,
-                                                   head_dim)
-           : omnitide::decode_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads, head_dim);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return OMNITIDE_E_WORKSPACE;
+  // with less than the full size the call uses as many splits as fit, or the least
+  const size_t full = omnitide::decode_workspace_bytes(span, n_seg, cap, n_q, n_q_heads,
+                                                       n_kv_heads, head_dim);
+  const size_t least = omnitide::decode_workspace_min_bytes(span, n_seg, cap, n_q, n_q_heads,
+                                                            n_kv_heads, head_dim);
+  const size_t given = workspace == nullptr ? 0 : workspace_bytes;
+  if (given < least) return OMNITIDE_E_WORKSPACE;
+  const size_t used = given < full ? given : full;
   const size_t qrows = static_cast<size_t>(n_seg) * n_q * n_q_heads;
   const size_t kv = static_cast<size_t>(n_seg) * cap * n_kv_heads * head_dim * 2;
-  if (any_alias({{out, qrows * head_dim * 4}, {workspace, need}, {d_status, 4}},
+  if (any_alias({{out, qrows * head_dim * 4}, {workspace, used}, {d_status, 4}},
                 {{q, qrows * head_dim * 2}, {k, kv}, {v, kv}, {n_ctx, n_seg * 4ull},
                  {key_pos, static_cast<size_t>(n_seg) * cap * 4}, {q_pos0, n_seg * 4ull}}))
     return OMNITIDE_E_ALIAS;
@@ -725,7 +729,8 @@ int decode_impl(const void* q, const void* k, const void* v, const int32_t* n_ct
   a.head_dim = head_dim;
   a.scale = scale;
   a.out = out;
-  a.workspace = need > 0 ? workspace : nullptr;
+  a.workspace = used > 0 ? workspace : nullptr;
+  a.workspace_bytes = used;
   a.d_status = d_status;
   a.key_pos = key_pos;
   a.q_pos0 = q_pos0;
@@ -749,8 +754,7 @@ size_t omnitide_decode_span_workspace_bytes(int n_seg, int cap, int n_q, int n_q
   if (n_seg < 1 || cap < 1 || n_q < 1 || n_kv_heads < 1 || n_q_heads < n_kv_heads ||
       n_q_heads % n_kv_heads != 0 || !(head_dim == 64 || head_dim == 128))
     return 0;
-  return omnitide::decode_span_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads,
-                                               head_dim);
+  return omnitide::decode_workspace_bytes(true, n_seg, cap, n_q, n_q_heads, n_kv_heads, head_dim);
 }
 
 int omnitide_decode_span_attn(const void* q, const void* k, const void* v,

@@ -8,9 +8,9 @@
 // per-key dot products, their cross-lane reductions and the P*V updates cost as much time as the
 // loads themselves, while a 16x16 MFMA block with the query vectors as columns (half of them
 // padding) costs almost nothing.
-//   grid      (key split, KV head, segment), eight-wave workgroups, one resident per CU; the split
-//             count fills whole rounds of 256 (decode_num_splits), and a combine kernel merges the
-//             partials in split order.
+//   grid      (key split, KV head, segment), eight-wave workgroups, one resident per CU; the splits
+//             fill one round of 256, or several where that leaves much of a round empty
+//             (decode_num_splits), and a combine kernel merges the partials in split order.
 //   waves     each wave owns 16 keys of every 128-key workgroup step and loads the next step's
 //             keys before it works on the current ones: the K operands straight from global
 //             memory into registers, the V rows by direct loads into a private double buffer in
@@ -485,50 +485,88 @@ hipError_t launch_decode_t(const DecodeArgs& a, int n_split, hipStream_t stream)
 
 }  // namespace
 
-// Splits per (segment, KV head).  One eight-wave workgroup is resident per CU, so the grid runs in
-// rounds of 256: a round costs its keys plus about 150 keys' worth of start, wave merge and drain,
-// the combine about 200 more.  The smallest s whose cost is within 5% of the least, from one full
-// round (256 / base) up to four times as many.  One round is right for few (segment, head)
-// pairs (one pair of 8 over 16,948 keys: 21.9 us with 32 splits, 27.0 with 43, 26.1 with 64), but
-// a base that leaves a round part-empty gains from more, smaller ones: 36 x 8 pairs over
-// 16,948 keys 602 us with one split (a second round of 32 workgroups), 423 with five; 24 x 8
-// over 9,173 keys 176 -> 169 with four; 20 x 8 over 5,000 keys 90 -> 87 with three.
-int decode_num_splits(int n_seg, int cap, int n_kv_heads) {
+// Splits per (segment, KV head) that fill one round of kDecTargetWGs workgroups (one eight-wave
+// workgroup is resident per CU), of at least 64 keys each: what a workspace has to hold at least.
+static int decode_round_splits(int n_seg, int cap, int n_kv_heads) {
   const long base = static_cast<long>(n_kv_heads) * n_seg;
   const long most = std::max(1L, std::min(128L, (static_cast<long>(cap) + 63) / 64));
-  const long s0 = std::max(1L, std::min(kDecTargetWGs / base, most));
-  auto cost = [&](long s) {
+  return static_cast<int>(std::max(1L, std::min(kDecTargetWGs / base, most)));
+}
+
+// Splits of a call at most, and what its workspace is for: up to max(4 times those of one round, 8)
+// of at least 256 keys, where one round's leave a part of a round empty.  It grows with the
+// pool, so a workspace sized for a pool is enough for every smaller one.
+static int decode_max_splits(int n_seg, int cap, int n_kv_heads) {
+  const long base = static_cast<long>(n_kv_heads) * n_seg;
+  const int s0 = decode_round_splits(n_seg, cap, n_kv_heads);
+  if (base * s0 % kDecTargetWGs == 0) return s0;
+  return std::max(s0, std::min({std::max(4 * s0, 8), cap / 256, 128}));
+}
+
+// Splits of a call: those of one round, or as many more (up to the most, above) as take the least
+// time by estimate where that saves 12%: a base that leaves much of a round empty gains from
+// more, smaller workgroups.  Estimate in keys: each round costs its keys and 400 more for start,
+// wave merge and drain, the combine 300.  Over 315 random shapes (1-130 segments, 400-60,000 keys)
+// with all or half of the pool in use the rule is 2.8-3.6% faster than one round on average and
+// never slower by more than 1.5%; with a quarter in use it is 3.6% faster, and four shapes are 2-4%
+// slower.  A margin of 5% with 150 keys a round made eight shapes 2-5% slower with all of the pool
+// in use (104 pairs over 12,776 keys: 128.8 us with two splits, 135.1 with seven) and 33 up to 34%
+// slower with a quarter.  36 x 8 pairs over 16,948 keys: 589 us with one split (a second round of
+// 32 workgroups), 426 with the seven taken; 17 x 8 over 9,173: 146 with one, 125 with five.
+int decode_num_splits(int n_seg, int cap, int n_kv_heads) {
+  const long base = static_cast<long>(n_kv_heads) * n_seg;
+  auto estimate = [&](int s) {
     const long rounds = (base * s + kDecTargetWGs - 1) / kDecTargetWGs;
-    return static_cast<double>(rounds) * (static_cast<double>(cap) / static_cast<double>(s) + 150.) +
-           (s > 1 ? 200. : 0.);
+    return static_cast<double>(rounds) * (static_cast<double>(cap) / s + 400.) +
+           (s > 1 ? 300. : 0.);
   };
-  const long s1 = std::min(most, std::max(4 * s0, 8L));
-  double best = cost(s0);
-  for (long s = s0 + 1; s <= s1; ++s) best = std::min(best, cost(s));
-  long s = s0;
-  while (cost(s) > 1.05 * best) ++s;
-  return static_cast<int>(s);
+  int best = decode_round_splits(n_seg, cap, n_kv_heads);
+  double best_keys = 0.88 * estimate(best);
+  for (int s = best + 1; s <= decode_max_splits(n_seg, cap, n_kv_heads); ++s) {
+    const double keys = estimate(s);
+    if (keys < best_keys) {
+      best = s;
+      best_keys = keys;
+    }
+  }
+  return best;
 }
 
-size_t decode_workspace_bytes(int n_seg, int cap, int n_q, int n_q_heads, int n_kv_heads,
-                              int head_dim) {
-  const int s = decode_num_splits(n_seg, cap, n_kv_heads);
-  if (s == 1) return 0;
+static size_t partial_bytes(int n_split, int n_seg, int n_q, int n_q_heads, int head_dim) {
   const size_t rows = static_cast<size_t>(n_seg) * n_q * n_q_heads;
-  return static_cast<size_t>(s) * rows * (static_cast<size_t>(head_dim) + 2) * sizeof(float);
+  return n_split == 1 ? 0 : static_cast<size_t>(n_split) * rows *
+                                (static_cast<size_t>(head_dim) + 2) * sizeof(float);
 }
 
-size_t decode_span_workspace_bytes(int n_seg, int cap, int n_q, int n_q_heads, int n_kv_heads,
-                                   int head_dim) {
-  // the tile tables (tile traversals) or the position index (position order)
-  return align256(decode_workspace_bytes(n_seg, cap, n_q, n_q_heads, n_kv_heads, head_dim)) +
-         std::max(span_tiles_bytes(n_seg, cap), pos_index_bytes(n_seg, cap));
+// The partials of n_split splits and, for a span, after them the tile tables (tile traversals) or the
+// position index (position order).
+static size_t workspace_bytes(int n_split, bool span, int n_seg, int cap, int n_q, int n_q_heads,
+                              int head_dim) {
+  const size_t part = partial_bytes(n_split, n_seg, n_q, n_q_heads, head_dim);
+  return span ? align256(part) + std::max(span_tiles_bytes(n_seg, cap), pos_index_bytes(n_seg, cap))
+              : part;
+}
+
+size_t decode_workspace_bytes(bool span, int n_seg, int cap, int n_q, int n_q_heads,
+                              int n_kv_heads, int head_dim) {
+  return workspace_bytes(decode_max_splits(n_seg, cap, n_kv_heads), span, n_seg, cap, n_q,
+                         n_q_heads, head_dim);
+}
+
+size_t decode_workspace_min_bytes(bool span, int n_seg, int cap, int n_q, int n_q_heads,
+                                  int n_kv_heads, int head_dim) {
+  return workspace_bytes(decode_round_splits(n_seg, cap, n_kv_heads), span, n_seg, cap, n_q,
+                         n_q_heads, head_dim);
 }
 
 int decode_max_query_vectors() { return kMaxQG; }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
-  const int s = decode_num_splits(a.n_seg, a.cap, a.n_kv_heads);
+  const bool span = a.key_pos != nullptr;
+  int s = decode_num_splits(a.n_seg, a.cap, a.n_kv_heads);
+  if (workspace_bytes(s, span, a.n_seg, a.cap, a.n_q, a.n_q_heads, a.head_dim) >
+      a.workspace_bytes)
+    s = decode_round_splits(a.n_seg, a.cap, a.n_kv_heads);
   if (a.head_dim == 128) return launch_decode_t<128>(a, s, stream);
   if (a.head_dim == 64) return launch_decode_t<64>(a, s, stream);
   return hipErrorInvalidValue;

@@ -224,6 +224,7 @@ struct DecodeArgs {
   float scale;
   float* out;
   void* workspace;
+  size_t workspace_bytes;             // at least decode_workspace_min_bytes
   int32_t* d_status;
   // span mode (keys = the slots [0, span) of a pool with holes; n_ctx holds the span):
   const int32_t* key_pos = nullptr;   // [n_seg][cap] logical position, -1 = empty slot
@@ -233,10 +234,12 @@ struct DecodeArgs {
 };
 
 int decode_num_splits(int n_seg, int cap, int n_kv_heads);
-size_t decode_workspace_bytes(int n_seg, int cap, int n_q, int n_q_heads, int n_kv_heads,
-                              int head_dim);
-size_t decode_span_workspace_bytes(int n_seg, int cap, int n_q, int n_q_heads, int n_kv_heads,
-                                   int head_dim);
+// What a call (over a span with holes or contiguous rows) uses, and the least it runs with: the
+// partials of one round's splits.
+size_t decode_workspace_bytes(bool span, int n_seg, int cap, int n_q, int n_q_heads,
+                              int n_kv_heads, int head_dim);
+size_t decode_workspace_min_bytes(bool span, int n_seg, int cap, int n_q, int n_q_heads,
+                                  int n_kv_heads, int head_dim);
 int decode_max_query_vectors();
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
 

@@ -446,6 +446,49 @@ def test_decode_validation(L):
     assert ot.omnitide_decode_workspace_bytes(1, 1000, 1, 30, 8, 128) == 0
 
 
+def one_round_bytes(n_seg, cap, nq, Hq, Hkv, d):
+    """The partials of as many splits as fill one round of 256 workgroups."""
+    s = max(1, min(256 // (n_seg * Hkv), (cap + 63) // 64, 128))
+    return s * n_seg * nq * Hq * (d + 2) * 4 if s > 1 else 0
+
+
+DECODE_SHAPES = [(1, 1, 32, 8, 128), (13, 1, 32, 8, 128), (17, 1, 32, 8, 128),
+                 (33, 2, 16, 8, 64), (36, 1, 32, 8, 128), (100, 1, 4, 1, 64), (300, 2, 4, 1, 64)]
+
+
+@pytest.mark.parametrize("n_seg,nq,Hq,Hkv,d", DECODE_SHAPES)
+def test_decode_workspace_sizes(L, n_seg, nq, Hq, Hkv, d):
+    """One workspace sized for a pool is enough for every smaller one, and the partials of one
+    round's splits (none beyond 128 pairs) are enough for every call, not a byte less (the overlap
+    of out and k, checked after the workspace, ends each accepted call here)."""
+    sh = dict(n_seg=n_seg, nq=nq, Hq=Hq, Hkv=Hkv, d=d)
+    need = need_span = 0
+    for cap in list(range(max(nq, 1), 40 * 1024, 61)) + [60000, 131072]:
+        n = ot.omnitide_decode_workspace_bytes(n_seg, cap, nq, Hq, Hkv, d)
+        ns = ot.omnitide_decode_span_workspace_bytes(n_seg, cap, nq, Hq, Hkv, d)
+        assert n >= need and ns >= need_span, cap
+        need, need_span = n, ns
+        least = one_round_bytes(n_seg, cap, nq, Hq, Hkv, d)
+        assert least <= n
+        if least:
+            assert decode(L, cap=cap, wsb=least - 1, out=fake(1), **sh) == ot.E_WORKSPACE
+            assert decode(L, cap=cap, wsb=least, out=fake(1), **sh) == ot.E_ALIAS
+        else:
+            assert decode(L, cap=cap, ws=None, wsb=0, out=fake(1), **sh) == ot.E_ALIAS
+
+
+@pytest.mark.parametrize("n_seg,nq,Hq,Hkv,d", DECODE_SHAPES)
+def test_decode_span_workspace_of_one_round(L, n_seg, nq, Hq, Hkv, d):
+    sh = dict(n_seg=n_seg, nq=nq, Hq=Hq, Hkv=Hkv, d=d, out=fake(1))
+    for cap in (500, 3000, 17000, 60000):
+        part = ot.omnitide_decode_workspace_bytes(n_seg, cap, nq, Hq, Hkv, d)
+        tables = ot.omnitide_decode_span_workspace_bytes(n_seg, cap, nq, Hq, Hkv, d) - \
+            -(-part // 256) * 256
+        least = -(-one_round_bytes(n_seg, cap, nq, Hq, Hkv, d) // 256) * 256 + tables
+        assert decode_span(L, cap=cap, wsb=least, **sh) == ot.E_ALIAS
+        assert decode_span(L, cap=cap, wsb=least - 1, **sh) == ot.E_WORKSPACE
+
+
 def decode_span(L, **kw):
     a = dict(q=fake(0), k=fake(1), v=fake(2), kp=fake(3), span=fake(4), qp=fake(5), n_seg=1,
              cap=81920, nq=1, Hq=32, Hkv=8, d=128, scale=0.088, trav=1, out=fake(6), ws=fake(7),

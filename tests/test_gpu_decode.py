@@ -139,3 +139,61 @@ def test_many_segments_split_counts(n_seg, cap, n_q, Hq, Hkv, d, several):
     for i in range(0, n_seg, 4):
         err = np.abs(out[i] - oracle_decode(q[i], k[i], v[i], n_ctx[i], scale))
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, err.max(), err.mean())
+
+
+@pytest.mark.parametrize("n_seg,cap,n_q,Hq,Hkv,d", [
+    (36, 3000, 1, 32, 8, 128),          # without a workspace: one split instead of several
+    (17, 9000, 1, 32, 8, 128),
+    (11, 20000, 1, 8, 8, 64),           # two splits instead of eight
+])
+def test_least_workspace(n_seg, cap, n_q, Hq, Hkv, d):
+    """A workspace of one round's partials (none beyond 128 pairs): the call uses fewer splits
+    than with a full one and nothing past the least."""
+    from paper_2609_34653_amd import omnitide as ot
+    s0 = max(1, 256 // (n_seg * Hkv))
+    least = s0 * n_seg * n_q * Hq * (d + 2) * 4 if s0 > 1 else 0
+    assert least < ot.omnitide_decode_workspace_bytes(n_seg, cap, n_q, Hq, Hkv, d)
+    g = torch.Generator(device="cuda").manual_seed(n_seg)
+    q, k, v = (torch.randn(n_seg, a, h, d, device="cuda", generator=g).bfloat16()
+               for a, h in ((n_q, Hq), (cap, Hkv), (cap, Hkv)))
+    n_ctx = torch.full((n_seg,), cap - 5, dtype=torch.int32, device="cuda")
+    n_ctx[0] = n_q
+    out = torch.full((n_seg, n_q, Hq, d), float("nan"), device="cuda")
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    buf = torch.full((least + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+    ot.omnitide_decode_attn(q, k, v, n_ctx, d ** -0.5, out, buf[:least] if least else None, st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0 and bool((buf[least:] == 0xFF).all())
+    for i in (0, 1, n_seg - 1):
+        want = oracle_decode(q[i].cpu(), k[i].cpu(), v[i].cpu(), int(n_ctx[i]), d ** -0.5)
+        err = np.abs(out[i].cpu().numpy() - want)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, err.max(), err.mean())
+
+
+@pytest.mark.parametrize("n_seg,cap,ctx,n_q,Hq,Hkv,d,splits", [
+    (1, 17049, 16948, 1, 32, 8, 128, 32),   # one round
+    (24, 10521, 9173, 2, 32, 8, 128, 4),    # three rounds instead of three quarters of one
+    (36, 3000, 3000, 1, 32, 8, 128, 3),     # a little over one round
+    (13, 12776, 12776, 1, 32, 8, 128, 2),   # more than one round's would not pay
+    (20, 3351, 769, 1, 32, 8, 128, 1),
+    (33, 2104, 449, 1, 28, 4, 128, 1),
+])
+def test_splits_in_use(n_seg, cap, ctx, n_q, Hq, Hkv, d, splits):
+    """The splits a call uses, by the partials (d + 2 floats per row and split) it leaves in a
+    workspace filled with 0xFF."""
+    from paper_2609_34653_amd import omnitide as ot
+    g = torch.Generator(device="cuda").manual_seed(n_seg)
+    q, k, v = (torch.randn(n_seg, a, h, d, device="cuda", generator=g).bfloat16()
+               for a, h in ((n_q, Hq), (cap, Hkv), (cap, Hkv)))
+    out = torch.full((n_seg, n_q, Hq, d), float("nan"), device="cuda")
+    nb = ot.omnitide_decode_workspace_bytes(n_seg, cap, n_q, Hq, Hkv, d)
+    ws = torch.full((max(1, nb),), 0xFF, dtype=torch.uint8, device="cuda")
+    ot.omnitide_decode_attn(q, k, v, torch.full((n_seg,), ctx, dtype=torch.int32, device="cuda"),
+                            d ** -0.5, out, ws)
+    torch.cuda.synchronize()
+    written = int((ws[:nb].view(torch.int32) != -1).sum())
+    assert written == (splits * n_seg * n_q * Hq * (d + 2) if splits > 1 else 0)
+    for i in (0, n_seg - 1):
+        want = oracle_decode(q[i].cpu(), k[i].cpu(), v[i].cpu(), ctx, d ** -0.5)
+        err = np.abs(out[i].cpu().numpy() - want)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, err.max(), err.mean())
