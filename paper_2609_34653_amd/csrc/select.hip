@@ -1,5 +1,5 @@
-// Budgeted whole-unit selection, one workgroup per segment.  Up to 128 units: a single wave
-// (select_small_kernel); beyond: 1024 threads (select_kernel).
+// Budgeted whole-unit selection, one workgroup per segment.  Up to 128 units (512 where there are
+// many segments): a single wave (select_small_kernel); beyond: 1024 threads (select_kernel).
 //
 // Groups (paper: must-keep, recent-context, selected-history):
 //   protected  units holding a system token (all kept; over budget -> OMNITIDE_E_BUDGET)
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   if (tid == 0) kept_tokens_g[seg] = t_sys + t_rec + taken;
 }
 
-// Single-wave variant for U <= 128 (every lane owns PER consecutive units): the same plan with
+// Single-wave variant for U <= 512 (every lane owns PER consecutive units): the same plan with
 // wave-level scans (no workgroup barriers) and, instead of a full sort, an MSD radix select of
 // the cut.  The walk "rank order, stop at the first misfit" keeps exactly the candidates whose
 // key exceeds the first misfit's key; the misfit is found digit by digit: a histogram of
@@ -511,16 +511,21 @@ hipError_t launch_select(const uint64_t* wsum, const int32_t* len, const int32_t
                          int32_t* kept_tokens, int32_t* status, hipStream_t stream) {
   // One wave up to 128 units, a workgroup beyond: the plan of a wave is bound by its instructions,
   // which grow with the units per lane (by graph replay: 37 units 3.1 us with one per lane, 6.7 with
-  // eight; 128 units 3.3 with two; 256 units 5.2 with four, 474 units 8.3 with eight, where the
-  // workgroup takes 4.6).
+  // eight; 128 units 3.4 with two; 256 units 5.2 with four and 4.5 by the workgroup, 474 units 8.3
+  // with eight and 4.6).  One workgroup's 16 waves have a CU to themselves up to 256 segments and two
+  // share it up to 512; with more the segments' waves are what fills the chip, and one each is
+  // enough (200 units, 384 segments: 8.1 us by the workgroup, 6.2 by a wave with four per lane; 358
+  // units, 512 segments: 8.8 and 10.4, 768: 12.1 and 11.2, 2,048: 26.8 and 17.1).
 #define OMNITIDE_SELECT_SMALL(PER)                                                              \
-  if (n_units <= PER * kWave)                                                                   \
+  if (n_units <= PER * kWave && (PER <= 2 || n_seg > (PER == 4 ? 256 : 512)))                   \
     hipLaunchKernelGGL(select_small_kernel<PER>, dim3(n_seg), dim3(kWave), 0, stream, wsum,     \
                        len, first, last, flags, n_units, budget, recent, score, keep,           \
                        kept_tokens, status);                                                    \
   else
   OMNITIDE_SELECT_SMALL(1)
   OMNITIDE_SELECT_SMALL(2)
+  OMNITIDE_SELECT_SMALL(4)
+  OMNITIDE_SELECT_SMALL(8)
 #undef OMNITIDE_SELECT_SMALL
 #define OMNITIDE_SELECT_CASE(PER)                                                               \
   if (n_units <= PER * kSelThreads)                                                             \
