@@ -1,5 +1,6 @@
-// OmniPick span plan: a census of the units, the plan, the slot mask.  Up to 512 units the plan is
-// made by every workgroup of the mask kernel (two launches), beyond by a kernel of its own.
+// OmniPick span plan: a census of the units, the plan, the slot mask.  Up to 512 units and not too
+// many workgroups the plan is made by every workgroup of the mask kernel (two launches), beyond by
+// a kernel of its own.
 //
 // 1. Census (one wave per unit).  The wave walks its unit's slots 1024 at a time (one aligned
 //    16-byte block of tags per lane) and
@@ -322,20 +323,23 @@ __device__ inline int plan_units(const SpanPlanIn& in, size_t base, const SpanWs
   return sc.sum(my_final);
 }
 
-// Plan of more than kMarkUnits units, one workgroup per segment.
+// The plan as a kernel of its own, one workgroup per segment: one wave up to kMarkUnits units
+// (WAVE), kPlanThreads beyond.
 constexpr int kPlanThreads = 1024;
 
-__global__ __launch_bounds__(kPlanThreads) void plan_spans_kernel(
+template <bool WAVE>
+__global__ __launch_bounds__(WAVE ? kWave : kPlanThreads) void plan_spans_kernel(
     SpanPlanIn in, int32_t* __restrict__ keep_len_g, int32_t* __restrict__ kept_g,
     uint8_t* __restrict__ ws, int32_t* __restrict__ status) {
-  __shared__ int32_t scr[kPlanThreads / kWave + 1];
+  constexpr int T = WAVE ? kWave : kPlanThreads;
+  __shared__ int32_t scr[T / kWave + 1];
   const int seg = blockIdx.x;
   const int tid = threadIdx.x;
-  const int per = (in.n_units + kPlanThreads - 1) / kPlanThreads;
+  const int per = (in.n_units + T - 1) / T;
   const size_t base = static_cast<size_t>(seg) * in.n_units;
   const SpanWs W = span_ws(ws, seg, in.n_slots, in.n_units);
   int ln[kMaxPer], kl[kMaxPer], tk[kMaxPer];
-  const int kept = plan_units<false>(in, base, W, tid, per, PlanScan<false>{scr}, ln, kl, tk);
+  const int kept = plan_units<WAVE>(in, base, W, tid, per, PlanScan<WAVE>{scr}, ln, kl, tk);
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) {
     const int u = tid * per + i;
@@ -381,11 +385,18 @@ __global__ __launch_bounds__(kMarkThreads) void span_mark_kernel(
 // Plan and mask in one launch for up to kMarkUnits units: wave 0 of every workgroup plans the
 // segment into LDS (about 2 us, in all workgroups at once) while the other waves' tags and codes
 // are on their way, then the workgroup marks its kMarkSlots slots; workgroup 0 writes the plan
-// out.  Latency-bound: as two launches the plan took 5.4 us and the mask 3.3 us at 358 units
-// and 81,920 slots.
+// out.  Latency-bound: one launch less where the host launches, and by graph replay 8-10% less for
+// the whole call where many segments have few units (36 x 32,768 slots in 38 units: 16.3 us
+// against 17.7 with a plan launch), the same for one segment (358 units and 81,920 slots: 10.4).
 constexpr int kMarkUnits = kWave * kMaxPer;
 constexpr int kMarkPer = 4;
 constexpr int kMarkSlots = kMarkThreads * kMarkPer;
+// Every workgroup repeats the plan, so its launch is saved only while all of them run at once (five
+// per CU: 1,280 of 8 x 1,024 slots in 39 units 17.6 us against 19.6 in two launches, 1,600 of them
+// 24.3 and 22.7) and the units they read between them are few (8 x 81,920 slots in 358 units,
+// 640 workgroups: 15.2 and 14.9; 36 x 81,920: 40.4 and 32.1).
+constexpr long kFusedMarks = 1280;
+constexpr long kFusedUnits = 65536;
 
 __global__ __launch_bounds__(kMarkThreads) void span_plan_mark_kernel(
     SpanPlanIn in, const int32_t* __restrict__ uid_g, int32_t* __restrict__ keep_len_g,
@@ -443,15 +454,20 @@ hipError_t launch_plan_spans(const SpanPlanArgs& a, hipStream_t stream) {
                      a.sink_audio, ws, a.d_status);
   const SpanPlanIn in{a.unit_len, a.unit_first, a.unit_last, a.unit_flags, a.n_slots,
                       a.n_units,  a.low,        a.high,      a.recent,     a.text_budget};
-  if (a.n_units <= kMarkUnits) {
+  const long marks = a.n_seg * ((static_cast<long>(a.n_slots) + kMarkSlots - 1) / kMarkSlots);
+  if (a.n_units <= kMarkUnits && marks <= kFusedMarks && marks * a.n_units <= kFusedUnits) {
     // one workgroup at least: it writes the plan also for a pool without slots
     const dim3 grid(std::max(1, (a.n_slots + kMarkSlots - 1) / kMarkSlots), a.n_seg);
     hipLaunchKernelGGL(span_plan_mark_kernel, grid, dim3(kMarkThreads), 0, stream, in, a.unit_id,
                        a.keep_len, a.kept_tokens, ws, a.keep_slot, a.d_status);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(plan_spans_kernel, dim3(a.n_seg), dim3(kPlanThreads), 0, stream, in,
-                     a.keep_len, a.kept_tokens, ws, a.d_status);
+  if (a.n_units <= kMarkUnits)
+    hipLaunchKernelGGL(plan_spans_kernel<true>, dim3(a.n_seg), dim3(kWave), 0, stream, in,
+                       a.keep_len, a.kept_tokens, ws, a.d_status);
+  else
+    hipLaunchKernelGGL(plan_spans_kernel<false>, dim3(a.n_seg), dim3(kPlanThreads), 0, stream, in,
+                       a.keep_len, a.kept_tokens, ws, a.d_status);
   if (a.n_slots > 0) {
     const dim3 mgrid((a.n_slots + kMarkThreads - 1) / kMarkThreads, a.n_seg);
     hipLaunchKernelGGL(span_mark_kernel, mgrid, dim3(kMarkThreads), 0, stream, a.unit_id,

@@ -121,6 +121,40 @@ def test_plan_parity_random(U, seed, mixed):
         assert int(kept[0]) == wkept
 
 
+@pytest.mark.parametrize("U,n_seg", [(3, 1300), (60, 640), (60, 700), (300, 40), (512, 12),
+                                     (512, 16), (513, 16)])
+def test_plan_many_segments(U, n_seg):
+    """Segment and unit counts on both sides of the one-launch plan's limits: four layouts of one
+    length (one trimmed, one malformed) over all segments."""
+    rng = np.random.default_rng(U + n_seg)
+    parts = [random_layout(rng, U) for _ in range(4)]
+    n = max(len(m) for _, m in parts)
+    for i, (sc, m) in enumerate(parts):                  # empty slots to one length
+        sc["unit_id"] = np.concatenate([sc["unit_id"], np.full(n - len(m), -1, np.int64)])
+        parts[i] = (sc, np.concatenate([m, np.zeros(n - len(m), np.int64)]))
+    bad = int(np.argmax(parts[3][0]["len"]))
+    parts[3][0]["last"][bad] += 1                        # its slots are not one run
+    total = int(parts[0][0]["len"].sum())
+    p = dict(high=total // 2, low=total // 3, recent=total // 8, sv=5, sa=2, tb=30)
+    order = [(i * 7) % 4 for i in range(n_seg)]
+    order[-1] = 0
+    cat = lambda k: np.concatenate([parts[o][0][k] for o in order])  # noqa: E731
+    got, mask, kept, status = gpu_plan(cat("len"), cat("first"), cat("last"), cat("flags"),
+                                       cat("unit_id"),
+                                       np.concatenate([parts[o][1] for o in order]), n, p, n_seg)
+    assert status == -17
+    got, mask = got.reshape(n_seg, U), mask.reshape(n_seg, n)
+    for o in range(4):
+        at = [i for i in range(n_seg) if order[i] == o]
+        if o == 3:
+            want, wmask, wkept = np.zeros(U), np.zeros(n), 0
+        else:
+            want, wmask, wkept = oracle_plan(parts[o][0], parts[o][1], p)
+        assert np.array_equal(got[at], np.tile(want, (len(at), 1)))
+        assert np.array_equal(mask[at], np.tile(wmask, (len(at), 1)))
+        assert np.all(kept[at] == wkept)
+
+
 def test_plan_long_spans():
     """Spans longer than one census step (1,024 slots), with sinks ending on, before and after
     step boundaries and text ranks carried across steps."""
