@@ -207,12 +207,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     return slot_of[min(block_base(it) + c16, row_end - 1)];
   };
   int slot_next = 0;
-  // Issues a block's loads.  base receives its first key (SPAN: the span's end for a block past
-  // the list, so that every key of it is out of range); SPAN: kp the position of key c16.
+  // Issues a block's loads.  SPAN: base receives its first key (the span's end for a block past
+  // the list, so that every key of it is out of range) and kp the position of key c16.
   auto issue = [&](int it, int buf, bf16x8 (&ka)[KC], int& kp, int& base) {
     int kb0 = block_base(it);
     if constexpr (SPAN) kb0 = tile_next >= 0 ? kKT * tile_next + kKB * (wave & 3) : 0;
-    base = SPAN && tile_next < 0 ? nctx : kb0;
+    if constexpr (SPAN) base = tile_next < 0 ? nctx : kb0;
     uint32_t kslot = 0;
     if constexpr (POS) kslot = min(static_cast<uint32_t>(slot_next), static_cast<uint32_t>(cap - 1));
     const int kr = POS ? static_cast<int>(kslot) : min(kb0 + c16, row_end - 1);
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_kernel(
     bf16x8(&kn)[KC] = B == 0 ? kB : kA;
     int& pn = B == 0 ? pB : pA;
     int& bn = B == 0 ? bB : bA;
-    const int kb0 = B == 0 ? bA : bB;
+    const int kb0 = !SPAN ? block_base(it) : B == 0 ? bA : bB;
     const bool more = it + 1 < n_it;
     floatx4 s = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
