@@ -174,8 +174,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_kernel(
   __shared__ int32_t kpos_lds[SPAN ? kKT : 1];     // positions of the current tile's keys
   __shared__ __attribute__((aligned(16))) int32_t slot_ring[POS ? 4 * kKT : 1];  // tiles t..t+3
 
-  // The per-segment words are on their way while the workgroup finds its place and asks for its
-  // query rows, which depend on none of them; the checks come after (ahead of any K or V access).
+  // The per-segment words are checked after the query rows, which depend on none of them, have been
+  // asked for (ahead of any K or V access).
   const int seg = blockIdx.y;
   int nctx = n_ctx_g[seg];                         // SPAN, POS: the span
   const int qp0 = SPAN || POS ? qpos0_g[seg] : 0;
