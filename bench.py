@@ -41,11 +41,11 @@ CSRC = os.path.join(ROOT, "paper_2609_34653_amd", "csrc")
 FETCH_SCALE, WRITE_SCALE = 2.000, 1.000
 COUNTER_TRAFFIC = {
     "score": (("score.hip", "common.h"), "8b69f17ec98290ac", 57031.8, 161.3),
-    "select": (("select.hip", "common.h"), "517593b9d29eaf2c", 10.0, 3.0),
+    "select": (("select.hip", "common.h"), "60e8f2105ffa1e00", 10.0, 3.0),
     "compact": (("compact.hip", "common.h"), "ccb8a1230099b6f9", 34176.7, 68118.6),
-    "attend": (("attention.hip", "combine.h", "common.h"), "7c6a4747382cc563", 54334.0, 43058.8),
+    "attend": (("attention.hip", "combine.h", "common.h"), "0beabcc5ee39d223", 54334.0, 43058.8),
     "compact_rope": (("compact.hip", "common.h"), "ccb8a1230099b6f9", 34231.5, 68034.4),
-    "decode": (("decode.hip", "combine.h", "common.h"), "f0d3bb732ebbb1c8", 34329.0, 536.0),
+    "decode": (("decode.hip", "combine.h", "common.h"), "240ce577039db8b2", 34329.1, 536.0),
 }
 
 
@@ -53,7 +53,7 @@ COUNTER_TRAFFIC = {
 # `bench.py --steps 5 --warmup 1 --no-cpu-baseline --no-graph --loop-steps 0 --no-other-configs`:
 # SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE / 8 XCDs x 1,024 SIMDs) per dispatch (the MFMA-only
 # probe reads 0.97 with this normalisation); keyed by the kernel's sources like COUNTER_TRAFFIC.
-MFMA_BUSY = (("attention.hip", "combine.h", "common.h"), "7c6a4747382cc563", 0.540)
+MFMA_BUSY = (("attention.hip", "combine.h", "common.h"), "0beabcc5ee39d223", 0.548)
 
 
 def mfma_busy(config):
