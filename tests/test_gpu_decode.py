@@ -120,14 +120,14 @@ def test_decode_workspace_reused_across_shapes():
 
 
 @pytest.mark.parametrize("n_seg,cap,n_q,Hq,Hkv,d,several", [
-    (33, 1500, 1, 16, 8, 64, True),     # just over one round of workgroups: split further
-    (20, 2500, 2, 16, 8, 128, True),    # a part-empty round
+    (33, 1500, 1, 16, 8, 64, True),     # just over one round of workgroups: could be split
+    (20, 2500, 2, 16, 8, 128, True),    # a part-empty round: could be split
     (33, 100, 1, 8, 8, 64, False),      # too short to split
     (128, 700, 1, 4, 2, 64, False),     # exactly one round
 ])
 def test_many_segments_split_counts(n_seg, cap, n_q, Hq, Hkv, d, several):
     """Segments x KV heads around and past one round of workgroups, ragged contexts down to
-    n_q keys (empty splits)."""
+    n_q keys; a workspace is asked for where more splits than one round's could pay."""
     from paper_2609_34653_amd import omnitide as ot
     rng = np.random.default_rng(n_seg + cap)
     n_ctx = [int(x) for x in rng.integers(n_q, cap + 1, size=n_seg)]
@@ -180,7 +180,7 @@ def test_least_workspace(n_seg, cap, n_q, Hq, Hkv, d):
 ])
 def test_splits_in_use(n_seg, cap, ctx, n_q, Hq, Hkv, d, splits):
     """The splits a call uses, by the partials (d + 2 floats per row and split) it leaves in a
-    workspace filled with 0xFF."""
+    workspace filled with 0xFF; the last of several segments holds n_q keys (empty splits)."""
     from paper_2609_34653_amd import omnitide as ot
     g = torch.Generator(device="cuda").manual_seed(n_seg)
     q, k, v = (torch.randn(n_seg, a, h, d, device="cuda", generator=g).bfloat16()
@@ -188,12 +188,13 @@ def test_splits_in_use(n_seg, cap, ctx, n_q, Hq, Hkv, d, splits):
     out = torch.full((n_seg, n_q, Hq, d), float("nan"), device="cuda")
     nb = ot.omnitide_decode_workspace_bytes(n_seg, cap, n_q, Hq, Hkv, d)
     ws = torch.full((max(1, nb),), 0xFF, dtype=torch.uint8, device="cuda")
-    ot.omnitide_decode_attn(q, k, v, torch.full((n_seg,), ctx, dtype=torch.int32, device="cuda"),
-                            d ** -0.5, out, ws)
+    n_ctx = torch.full((n_seg,), ctx, dtype=torch.int32, device="cuda")
+    n_ctx[1:][-1:] = n_q
+    ot.omnitide_decode_attn(q, k, v, n_ctx, d ** -0.5, out, ws)
     torch.cuda.synchronize()
     written = int((ws[:nb].view(torch.int32) != -1).sum())
     assert written == (splits * n_seg * n_q * Hq * (d + 2) if splits > 1 else 0)
     for i in (0, n_seg - 1):
-        want = oracle_decode(q[i].cpu(), k[i].cpu(), v[i].cpu(), ctx, d ** -0.5)
+        want = oracle_decode(q[i].cpu(), k[i].cpu(), v[i].cpu(), int(n_ctx[i]), d ** -0.5)
         err = np.abs(out[i].cpu().numpy() - want)
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (i, err.max(), err.mean())
